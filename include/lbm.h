@@ -285,6 +285,16 @@ int lbm_mlp_forward(const float* d_params, const float* d_x, float* d_y, int64_t
 int lbm_mlp_gradient(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
                      float* d_grad, float* d_loss, void* hip_stream);
 
+/* The same with a caller-owned device workspace (lbm_mlp_gradient_work_size
+ * bytes, which may be 0; float aligned; LBM_EWORKSPACE if missing or too small),
+ * which lets the rows spread over the whole GPU: lbm_mlp_gradient, without one,
+ * runs on a single workgroup.  The sums of a given n are taken in a fixed
+ * order.  The workspace is free again when the call's work on hip_stream is
+ * done. */
+int lbm_mlp_gradient_work_size(int32_t n, size_t* bytes);
+int lbm_mlp_gradient_in(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
+                        float* d_grad, float* d_loss, void* d_work, size_t bytes, void* hip_stream);
+
 /* `steps` Adam steps (Kingma & Ba 2015; beta 0.9, 0.999, eps 1e-8, learning
  * rate lr) on mini-batches of `batch` rows (a multiple of 64) taken in order,
  * cycling through the n rows: step s uses rows (s * batch + j) mod n.  step0

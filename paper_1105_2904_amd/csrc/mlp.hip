@@ -3,12 +3,14 @@
 //
 //   k_mlp_forward  persistent grid, one 16-sample tile per wave at a time,
 //                  weights staged once per workgroup in LDS.
-//   k_mlp_train    one workgroup of four waves: forward, loss, backward and
-//                  weight gradients on the matrix cores for a mini-batch,
-//                  fixed-order cross-wave sums, Adam update of the FP32
-//                  master weights and their FP16 tiles; a loop over steps.
-//                  With grad != nullptr it returns the gradient of the loss
-//                  over all rows instead of updating.
+//   k_mlp_train    one workgroup of sixteen waves, a loop over Adam steps:
+//                  each wave takes a 16-sample tile of the mini-batch through
+//                  forward, loss and backward, then owns one 16 x 16 tile of
+//                  the weight gradients, contracted over every sample of the
+//                  batch, and the Adam state of those weights.
+//   k_mlp_grad     the same pass without the update, on as many workgroups
+//                  as the rows fill; k_mlp_grad_sum adds their sums in a
+//                  fixed order.
 // Loss over B rows: L = (1/B) sum_rows sum_o (y - t)^2.  The backward signals
 // are multiplied by the loss scale S before their FP16 rounding and the
 // weight gradients divided by S again, in FP32.
@@ -27,36 +29,6 @@ using mlp::f4;
 using mlp::h4;
 
 constexpr int kWaves = 4;
-
-struct TrainShared {
-  mlp::Weights w;
-  _Float16 tr[kWaves][16 * 16];  // per-wave transpose scratch
-  float red[mlp::kParams];       // gradient summed over the waves, flat order
-  float lsum[kWaves];
-};
-
-// A tile in accumulator layout (lane l: M[4(l/16)+i][l%16]) handed back in
-// operand layout of its transpose (lane l: M[l%16][4(l/16)+i]) through the
-// wave's own LDS scratch; only the wave's lanes touch it.
-__device__ __forceinline__ h4 transpose(h4 v, _Float16* tr, int lane) {
-  const int r = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; i++) tr[(4 * g + i) * 16 + r] = v[i];
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  h4 t;
-#pragma unroll
-  for (int i = 0; i < 4; i++) t[i] = tr[r * 16 + 4 * g + i];
-  __builtin_amdgcn_wave_barrier();
-  return t;
-}
-
-__device__ __forceinline__ float sum16(float v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X,
                                                      float* __restrict__ Y, int64_t n) {
@@ -94,194 +66,482 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P
   }
 }
 
-// rows of tile tt of wave wv in step s: training cycles through the data in
-// order, batch rows per step; the gradient pass covers rows 0 .. n-1 once.
-__device__ __forceinline__ int64_t tile_row(bool full, int64_t n, int64_t batch, int64_t step, int tile, int j,
-                                            bool& valid) {
-  if (full) {
-    const int64_t row = (int64_t)tile * 16 + j;
-    valid = row < n;
-    return valid ? row : 0;
-  }
-  valid = true;
-  return (step * batch + (int64_t)tile * 16 + j) % n;
+// ---------------------------------------------------------------------------
+// Gradient pass: kTiles waves, one 16-sample tile each, then one output tile
+// of the weight gradients each.
+//
+// Bound: the latency of one CU's dependent phases, not its units.  With four
+// waves, each holding every weight-gradient tile and adding them to a shared
+// sum one wave after the other, a step of 256 rows took 56 us; sixteen waves
+// (four per SIMD) hide the tanh and LDS latencies of each other, and a wave
+// that owns an output tile needs no cross-wave sum at all.  The activations
+// and backward signals of every tile pass through LDS once, transposed there
+// into the operand order of the gradient products (the samples are the
+// contraction).  500 steps of 256 rows: 28.5 -> 5.8 ms (11.5 us a step: about
+// 15k cycles of tiles, 5k of products, 5k of Adam); the gradient of 44,672
+// rows on 175 workgroups 4,982 -> 22.5 us.
+// ---------------------------------------------------------------------------
+constexpr int kTiles = 16;              // tiles of a pass, and waves of the workgroup
+constexpr int kTrainThreads = 64 * kTiles;
+constexpr int kChains = 4;              // partial sums per output: tile t adds to chain t % kChains
+
+// One tile's part in the gradient products, [feature][sample].  In rows with
+// bit 3 set the two halves of the 16 samples trade places: an operand read
+// takes 4 samples of each of 16 rows, and rows r and r + 8 would start in the
+// same LDS bank.
+struct TileSignals {
+  _Float16 h1[mlp::kHid][16], h2[mlp::kHid][16];  // hidden activations
+  _Float16 g1[mlp::kHid][16], g2[mlp::kHid][16];  // dL/dz1, dL/dz2 (scaled by S)
+  _Float16 x[mlp::kIn][16];                       // inputs
+  _Float16 gy[mlp::kOut][16];                     // dL/dy (scaled by S)
+  float e[mlp::kOut][16];                         // y - t
+};
+struct TrainShared {
+  mlp::Weights w;
+  TileSignals t[kTiles];
+};
+static_assert(sizeof(TrainShared) <= 160 * 1024, "one workgroup's LDS");
+
+// Place of sample j (or of the quad of samples 4q) in row `row`.
+__device__ __forceinline__ int at_sample(int row, int j) { return j ^ (row & 8); }
+
+// A tile in accumulator layout (lane l: M[4(l/16)+i][l%16]) into rows
+// 16 mt .. 16 mt + 15 of a [feature][sample] array; read back four samples at
+// a time, it is the operand of the products over samples.
+__device__ __forceinline__ void put_tile(_Float16 (*dst)[16], int mt, h4 v, int lane) {
+  const int r = lane & 15, g = lane >> 4, at = at_sample(4 * g, r);
+#pragma unroll
+  for (int i = 0; i < 4; i++) dst[16 * mt + 4 * g + i][at] = v[i];
 }
 
-__global__ __launch_bounds__(256) void k_mlp_train(float* __restrict__ P, float* __restrict__ Mo,
-                                                   float* __restrict__ Vo, const float* __restrict__ X,
-                                                   const float* __restrict__ T, int64_t n, int batch, int steps,
-                                                   int step0, float lr, float S, float* __restrict__ loss_out,
-                                                   float* __restrict__ grad) {
-  __shared__ TrainShared sh;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// The inputs and targets of one tile's rows as the lanes of its wave hold
+// them: features 4g .. 4g+3 (g < 2) and, at g = 0, the targets of row `row`.
+struct TileRows {
+  f4 x;
+  float t[2];
+};
+__device__ __forceinline__ TileRows load_rows(const float* __restrict__ X, const float* __restrict__ T, int64_t row,
+                                              bool valid, int lane) {
+  const int g = lane >> 4;
+  TileRows v = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f}};
+  if (valid && g < 2) {
+    const float* p = X + row * mlp::kIn + 4 * g;
+    v.x = f4{p[0], p[1], p[2], p[3]};
+  }
+  if (valid && g == 0) {
+    v.t[0] = T[row * mlp::kOut];
+    v.t[1] = T[row * mlp::kOut + 1];
+  }
+  return v;
+}
+
+// Forward, loss and backward of one tile; its signals to `ts`.
+__device__ __forceinline__ void tile_signals(const mlp::Weights& w, TileSignals& ts, const TileRows& in, bool valid,
+                                             float S, float Btot, int lane) {
   const int r = lane & 15, g = lane >> 4;
-  const bool full = grad != nullptr;
-  const int tiles = full ? (int)((n + 15) / 16) : batch / 16;  // tiles of the pass
-  const float Btot = full ? (float)n : (float)batch;
-  _Float16* tr = sh.tr[wv];
-  mlp::load_weights(sh.w, P, tid, 256);
+  h4 xb;
+#pragma unroll
+  for (int i = 0; i < 4; i++) xb[i] = (_Float16)in.x[i];
+  h4 h1[4], h2[4];
+  f4 y;
+  mlp::forward_tile(w, xb, h1, h2, y, lane);
+  // output error, scaled for the FP16 backward signals (lanes 0..15)
+  h4 gy = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
+  if (g == 0) {
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const float e = valid ? y[i] + w.b3[i] - in.t[i] : 0.0f;
+      if (valid) gy[i] = (_Float16)(S * 2.0f * e / Btot);
+      ts.e[i][r] = e;
+      ts.gy[i][r] = gy[i];
+    }
+  }
+  if (g < 2) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) ts.x[4 * g + i][r] = xb[i];
+  }
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    put_tile(ts.h1, mt, h1[mt], lane);
+    put_tile(ts.h2, mt, h2[mt], lane);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // dL/dz2 = (W3 dL/dy) * (1 - h2^2),  dL/dz1 = (W2 dL/dz2) * (1 - h1^2)
+  h4 gz2[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc = mlp::mma(mlp::ld4(&w.w3[16 * mt + r][4 * g]), gy, acc);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const float hv = (float)h2[mt][i];
+      gz2[mt][i] = (_Float16)(acc[i] * (1.0f - hv * hv));
+    }
+    put_tile(ts.g2, mt, gz2[mt], lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) acc = mlp::mma(mlp::ld4(&w.w2[16 * mt + r][16 * kt + 4 * g]), gz2[kt], acc);
+    h4 gz1;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const float hv = (float)h1[mt][i];
+      gz1[i] = (_Float16)(acc[i] * (1.0f - hv * hv));
+    }
+    put_tile(ts.g1, mt, gz1, lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The gradient sums one thread owns (scaled by S), in kChains partial sums
+// each: a 16 x 16 tile of W2 per wave (f4 per lane), a tile of W1 in waves
+// 0..3 and of W3 in waves 4..7, the bias sums and the loss.
+struct GradSums {
+  f4 w2[kChains], w13[kChains];
+};
+// Bias sums: lane = 16 chain + 4 feature + quad of a wave sums, over the tiles
+// of its chain, samples 4 quad .. 4 quad + 3 of bias feature 64 layer +
+// 4 wave + feature (layer 0: b1, layer 1: b2); wave 8 also b3 and the loss.
+struct BiasSums {
+  f4 b[2], b3;
+  float loss[4];
+};
+
+__device__ __forceinline__ f4 widen(h4 v) { return f4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]}; }
+
+// Adds tiles 0 .. nt-1 of a pass (nt a multiple of kChains).  The loop over
+// groups of tiles stays a loop: unrolled, the addresses of every tile, which
+// lie past an LDS instruction's 64 KiB offset, were kept in registers.
+__device__ __forceinline__ void add_tiles(const TrainShared& sh, int nt, int wv, int lane, GradSums& s, BiasSums& b) {
+  const int r = lane & 15, g = lane >> 4;
+  const int mt = wv >> 2, kt = wv & 3;
+  const h4 zero = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
+  const int row = at_sample(r, 4 * g);  // this lane's quad in rows 16 k + r
+  const int ch = lane >> 4, fe = (lane >> 2) & 3, q = lane & 3;
+  const int fr = 4 * wv + fe, fq = at_sample(fr, 4 * q);
+#pragma unroll 1
+  for (int t0 = 0; t0 < nt; t0 += kChains) {
+    const TileSignals* ts = sh.t + t0;
+    const TileSignals& tb = ts[ch];
+    const h4 b1 = mlp::ld4(&tb.g1[fr][fq]), b2 = mlp::ld4(&tb.g2[fr][fq]);
+#pragma unroll
+    for (int c = 0; c < kChains; c++)
+      s.w2[c] = mlp::mma(mlp::ld4(&ts[c].g2[16 * mt + r][row]), mlp::ld4(&ts[c].h1[16 * kt + r][row]), s.w2[c]);
+    if (wv < 4) {
+#pragma unroll
+      for (int c = 0; c < kChains; c++) {
+        const h4 x = mlp::ld4(&ts[c].x[r & 7][4 * g]);
+        s.w13[c] = mlp::mma(mlp::ld4(&ts[c].g1[16 * wv + r][row]), r < mlp::kIn ? x : zero, s.w13[c]);
+      }
+    } else if (wv < 8) {
+#pragma unroll
+      for (int c = 0; c < kChains; c++) {
+        const h4 gy = mlp::ld4(&ts[c].gy[r & 1][4 * g]);
+        s.w13[c] = mlp::mma(r < mlp::kOut ? gy : zero, mlp::ld4(&ts[c].h2[16 * (wv - 4) + r][row]), s.w13[c]);
+      }
+    } else if (wv == 8) {
+      b.b3 += widen(mlp::ld4(&tb.gy[fe & 1][4 * q]));  // features 0 and 1; the rest is not used
+#pragma unroll
+      for (int k = 0; k < 4; k++)
+#pragma unroll
+        for (int i = 0; i < mlp::kOut; i++) b.loss[k] += tb.e[i][4 * q + k] * tb.e[i][4 * q + k];
+    }
+    b.b[0] += widen(b1);
+    b.b[1] += widen(b2);
+  }
+}
+
+// The chains of one output added in order.
+__device__ __forceinline__ float chain_sum(const f4 (&s)[kChains], int i) {
+  float v = 0.f;
+#pragma unroll
+  for (int c = 0; c < kChains; c++) v += s[c][i];
+  return v;
+}
+// Sum over the 16 samples (quads, then within the quad) and then over the
+// chains in order, of a per-lane quad of sample sums; every lane of a feature
+// gets it.
+__device__ __forceinline__ float sample_sum(f4 v, int lane) {
+#pragma unroll
+  for (int o = 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] += __shfl_xor(v[k], o);
+  const float s = (v[0] + v[2]) + (v[1] + v[3]);
+  float tot = 0.f;
+#pragma unroll
+  for (int c = 0; c < kChains; c++) tot += __shfl(s, 16 * c + (lane & 15));
+  return tot;
+}
+
+// Parameters a thread owns, as flat indices: W2[kr][4 consecutive columns]
+// from w2; four consecutive columns of a W1 row (waves 0..3, r < 8) or the two
+// columns of a W3 row (waves 4..7, g = 0) from w13, n13 of them; and one bias
+// (b, -1 for none): in the lanes of chain 0, quad 0 of a feature holds its b1,
+// quad 1 its b2, and in wave 8 quad 2 of the first two features b3.
+struct Owned {
+  int w2, w13, n13, b;
+};
+__device__ __forceinline__ Owned owned_params(int wv, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  Owned o;
+  o.w2 = mlp::oW2 + (16 * (wv & 3) + r) * mlp::kHid + 16 * (wv >> 2) + 4 * g;
+  o.w13 = wv < 4 ? mlp::oW1 + r * mlp::kHid + 16 * wv + 4 * g : mlp::oW3 + (16 * (wv & 3) + r) * mlp::kOut;
+  o.n13 = wv < 4 ? (r < mlp::kIn ? 4 : 0) : (wv < 8 && g == 0 ? mlp::kOut : 0);
+  const int fe = lane >> 2, q = lane & 3;
+  o.b = -1;
+  if (lane < 16) {
+    if (q == 0) o.b = mlp::oB1 + 4 * wv + fe;
+    if (q == 1) o.b = mlp::oB2 + 4 * wv + fe;
+    if (q == 2 && wv == 8 && fe < mlp::kOut) o.b = mlp::oB3 + fe;
+  }
+  return o;
+}
+// The sum of the bias a lane owns (see Owned; every lane of a feature holds
+// all of its sums).
+__device__ __forceinline__ float bias_sum(const BiasSums& bs, int wv, int lane) {
+  const float s1 = sample_sum(bs.b[0], lane), s2 = sample_sum(bs.b[1], lane);
+  const float s3 = wv == 8 ? sample_sum(bs.b3, lane) : 0.f;
+  const int q = lane & 3;
+  return q == 0 ? s1 : q == 1 ? s2 : s3;
+}
+
+__device__ __forceinline__ void clear(GradSums& s, BiasSums& b) {
+  const f4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < kChains; c++) s.w2[c] = s.w13[c] = z;
+  b.b[0] = b.b[1] = b.b3 = z;
+#pragma unroll
+  for (int k = 0; k < 4; k++) b.loss[k] = 0.f;
+}
+
+// x / d for a divisor shared by many: inv is 1/d correctly rounded, and one
+// remainder step makes the quotient correctly rounded too (Markstein, IBM J.
+// Res. Dev. 34, 1990), four instructions fewer than a division.
+__device__ __forceinline__ float div_by(float x, float d, float inv) {
+  const float q = x * inv;
+  return __builtin_fmaf(__builtin_fmaf(-q, d, x), inv, q);
+}
+// Constants of one Adam step (Kingma & Ba 2015): learning rate, the bias
+// corrections and their reciprocals.
+struct AdamStep {
+  float lr, c1, c2, i1, i2;
+};
+// One FP32 master weight and its moments.
+struct AdamState {
+  float p, m, v;
+};
+__device__ __forceinline__ void adam(AdamState& a, float gk, const AdamStep& s) {
+#pragma clang fp contract(off)
+  a.m = __builtin_fmaf(0.9f, a.m, 0.1f * gk);
+  a.v = __builtin_fmaf(0.999f, a.v, 0.001f * gk * gk);
+  a.p = a.p - s.lr * div_by(a.m, s.c1, s.i1) / (sqrtf(div_by(a.v, s.c2, s.i2)) + 1e-8f);
+}
+
+__device__ __forceinline__ AdamState load_state(const float* P, const float* Mo, const float* Vo, int k, bool has) {
+  return has ? AdamState{P[k], Mo[k], Vo[k]} : AdamState{0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ void store_state(float* P, float* Mo, float* Vo, int k, const AdamState& a) {
+  P[k] = a.p;
+  Mo[k] = a.m;
+  Vo[k] = a.v;
+}
+
+// `steps` Adam steps: step s takes rows (s * batch + j) mod n.  The master
+// weights and moments stay in the registers of their owners; the FP16 tiles
+// in LDS follow every update.  ONE: the batch is one pass of tiles, so the
+// sums need not live across the tile phase.
+template <bool ONE>
+__global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__ P, float* __restrict__ Mo,
+                                                             float* __restrict__ Vo, const float* __restrict__ X,
+                                                             const float* __restrict__ T, int n, int batch, int steps,
+                                                             int step0, float lr, float S,
+                                                             float* __restrict__ loss_out) {
+  __shared__ TrainShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = batch / 16;
+  const float Btot = (float)batch;
+  const Owned own = owned_params(wv, lane);
+  AdamState s2[4], s13[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    s2[i] = load_state(P, Mo, Vo, own.w2 + i, true);
+    s13[i] = load_state(P, Mo, Vo, own.w13 + i, i < own.n13);
+  }
+  AdamState sb = load_state(P, Mo, Vo, own.b, own.b >= 0);
+  // a division by a power of two is the multiplication by its reciprocal
+  const bool s_pow2 = __float_as_uint(S) % (1u << 23) == 0 && S >= 0x1p-100f && S <= 0x1p100f;
+  const float s_inv = 1.0f / S;
+  auto unscale = [&](float v) { return s_pow2 ? v * s_inv : v / S; };
+  AdamStep ahead = {};  // of step s - s % 64 + lane
+  mlp::load_weights(sh.w, P, tid, kTrainThreads);
+  // the row of this lane's sample in tile `tile` of the step whose first row is `from`
+  auto row_of = [&](uint32_t from, int tile) {
+    return (int64_t)((from + (uint32_t)(16 * tile + (lane & 15))) % (uint32_t)n);
+  };
+  uint32_t base = (uint32_t)(((uint64_t)step0 * (uint32_t)batch) % (uint32_t)n);
+  TileRows next = load_rows(X, T, row_of(base, wv), wv < tiles, lane);
   __syncthreads();
   for (int s = 0; s < steps; s++) {
-    const int64_t step = (int64_t)step0 + s;
-    f4 dW2[4][4], dW1[4], dW3[4];
-    float db1[4][4], db2[4][4], db3[2] = {0.f, 0.f};
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      dW1[a] = f4{0.f, 0.f, 0.f, 0.f};
-      dW3[a] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int b = 0; b < 4; b++) {
-        dW2[a][b] = f4{0.f, 0.f, 0.f, 0.f};
-        db1[a][b] = 0.f;
-        db2[a][b] = 0.f;
-      }
-    }
-    float lsum = 0.f;
-    for (int tt = wv; tt < tiles; tt += kWaves) {
-      bool valid;
-      const int64_t row = tile_row(full, n, batch, step, tt, r, valid);
-      h4 xb;
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-        xb[i] = (g < 2 && valid) ? (_Float16)X[row * mlp::kIn + 4 * g + i] : (_Float16)0.0f;
-      h4 h1[4], h2[4];
-      f4 y;
-      mlp::forward_tile(sh.w, xb, h1, h2, y, lane);
-      // output error, scaled for the FP16 backward signals (lanes 0..15)
-      h4 gy = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
-      if (g == 0 && valid) {
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-          const float e = y[i] + sh.w.b3[i] - T[row * mlp::kOut + i];
-          lsum += e * e;
-          gy[i] = (_Float16)(S * 2.0f * e / Btot);
-        }
-      }
-      // dL/dz2 = (W3 dL/dy) * (1 - h2^2),  dL/dz1 = (W2 dL/dz2) * (1 - h1^2)
-      h4 gz2[4], gz1[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++) {
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mlp::mma(mlp::ld4(&sh.w.w3[16 * mt + r][4 * g]), gy, acc);
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const float hv = (float)h2[mt][i];
-          gz2[mt][i] = (_Float16)(acc[i] * (1.0f - hv * hv));
-        }
-      }
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++) {
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kt = 0; kt < 4; kt++) acc = mlp::mma(mlp::ld4(&sh.w.w2[16 * mt + r][16 * kt + 4 * g]), gz2[kt], acc);
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const float hv = (float)h1[mt][i];
-          gz1[mt][i] = (_Float16)(acc[i] * (1.0f - hv * hv));
-        }
-      }
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          db1[mt][i] += (float)gz1[mt][i];
-          db2[mt][i] += (float)gz2[mt][i];
-        }
-      db3[0] += (float)gy[0];
-      db3[1] += (float)gy[1];
-      // weight gradients: the samples of the tile are the contraction
-      h4 h1t[4];
-#pragma unroll
-      for (int kt = 0; kt < 4; kt++) h1t[kt] = transpose(h1[kt], tr, lane);
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++) {
-        const h4 a = transpose(gz2[mt], tr, lane);
-#pragma unroll
-        for (int kt = 0; kt < 4; kt++) dW2[mt][kt] = mlp::mma(a, h1t[kt], dW2[mt][kt]);
-      }
-      // inputs as B: lane l holds feature l%16 of sample 4(l/16)+i
-      h4 xs;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        bool v2;
-        const int64_t rj = tile_row(full, n, batch, step, tt, 4 * g + i, v2);
-        xs[i] = (r < mlp::kIn && v2) ? (_Float16)X[rj * mlp::kIn + r] : (_Float16)0.0f;
-      }
-#pragma unroll
-      for (int mt = 0; mt < 4; mt++) dW1[mt] = mlp::mma(transpose(gz1[mt], tr, lane), xs, dW1[mt]);
-      const h4 gyt = transpose(gy, tr, lane);
-#pragma unroll
-      for (int kt = 0; kt < 4; kt++) dW3[kt] = mlp::mma(gyt, transpose(h2[kt], tr, lane), dW3[kt]);
-    }
-    // bias sums over the 16 samples of each lane group
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        db1[mt][i] = sum16(db1[mt][i]);
-        db2[mt][i] = sum16(db2[mt][i]);
-      }
-    db3[0] = sum16(db3[0]);
-    db3[1] = sum16(db3[1]);
-    float ls = lsum;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o);
-    if (lane == 0) sh.lsum[wv] = ls;
-    // waves add their sums in wave order
-    for (int w = 0; w < kWaves; w++) {
-      if (wv == w) {
-        auto put = [&](int k, float v) { sh.red[k] = (w == 0 ? 0.f : sh.red[k]) + v; };
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-          for (int kt = 0; kt < 4; kt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) put(mlp::oW2 + (16 * kt + r) * mlp::kHid + 16 * mt + 4 * g + i, dW2[mt][kt][i]);
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-          for (int i = 0; i < 4; i++) {
-            if (r < mlp::kIn) put(mlp::oW1 + r * mlp::kHid + 16 * mt + 4 * g + i, dW1[mt][i]);
-            if (r == 0) {
-              put(mlp::oB1 + 16 * mt + 4 * g + i, db1[mt][i]);
-              put(mlp::oB2 + 16 * mt + 4 * g + i, db2[mt][i]);
-            }
-          }
-        if (g == 0) {
-#pragma unroll
-          for (int kt = 0; kt < 4; kt++)
-#pragma unroll
-            for (int i = 0; i < 2; i++) put(mlp::oW3 + (16 * kt + r) * mlp::kOut + i, dW3[kt][i]);
-          if (r == 0) {
-            put(mlp::oB3, db3[0]);
-            put(mlp::oB3 + 1, db3[1]);
-          }
-        }
-      }
+    GradSums gs;
+    BiasSums bs;
+    if constexpr (!ONE) clear(gs, bs);
+    const uint32_t base1 = (base + (uint32_t)batch) % (uint32_t)n;
+    for (int t0 = 0; t0 < tiles; t0 += kTiles) {
+      const TileRows in = next;
+      // the next pass's rows, or the next step's first, load meanwhile
+      const bool last = ONE || t0 + kTiles >= tiles;
+      const int tn = last ? wv : t0 + kTiles + wv;
+      next = load_rows(X, T, row_of(last ? base1 : base, tn), tn < tiles, lane);
+      if (t0 + wv < tiles) tile_signals(sh.w, sh.t[wv], in, true, S, Btot, lane);
       __syncthreads();
+      if constexpr (ONE) clear(gs, bs);
+      add_tiles(sh, min(kTiles, tiles - t0), wv, lane, gs, bs);
+      if (last) break;
+      __syncthreads();  // the tiles are free again
     }
-    const float loss = (sh.lsum[0] + sh.lsum[1] + sh.lsum[2] + sh.lsum[3]) / Btot;
-    if (full) {
-      for (int k = tid; k < mlp::kParams; k += 256) grad[k] = sh.red[k] / S;
-      if (tid == 0 && loss_out) loss_out[0] = loss;
-      return;
+    base = base1;
+    if (wv == 8) {
+      const float loss = sample_sum(f4{bs.loss[0], bs.loss[1], bs.loss[2], bs.loss[3]}, lane) / Btot;
+      if (lane == 0 && loss_out) loss_out[s] = loss;
     }
-    if (tid == 0 && loss_out) loss_out[s] = loss;
-    // Adam (Kingma & Ba 2015) on the FP32 master weights
-    const float tstep = (float)(step + 1);
-    const float c1 = 1.0f - powf(0.9f, tstep), c2 = 1.0f - powf(0.999f, tstep);
-    for (int k = tid; k < mlp::kParams; k += 256) {
-      const float gk = sh.red[k] / S;
-      const float m = 0.9f * Mo[k] + 0.1f * gk;
-      const float v = 0.999f * Vo[k] + 0.001f * gk * gk;
-      Mo[k] = m;
-      Vo[k] = v;
-      const float p = P[k] - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
-      P[k] = p;
-      mlp::put_param(sh.w, k, p);
+    // the constants of 64 steps at a time, one per lane
+    if (s % 64 == 0) {
+      const float tstep = (float)((int64_t)step0 + s + lane + 1);
+      ahead.c1 = 1.0f - powf(0.9f, tstep);
+      ahead.c2 = 1.0f - powf(0.999f, tstep);
+      ahead.i1 = 1.0f / ahead.c1;
+      ahead.i2 = 1.0f / ahead.c2;
+    }
+    auto of_step = [&](float v) {
+      return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), s % 64));
+    };
+    const AdamStep as = {lr, of_step(ahead.c1), of_step(ahead.c2), of_step(ahead.i1), of_step(ahead.i2)};
+    const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      adam(s2[i], unscale(chain_sum(gs.w2, i)), as);
+      const _Float16 h = (_Float16)s2[i].p;
+      const int kr = 16 * (wv & 3) + r, c = 16 * (wv >> 2) + 4 * g + i;  // W2[kr][c]
+      sh.w.w2t[c][kr] = h;
+      sh.w.w2[kr][c] = h;
+    }
+    if (wv < 8) {
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        if (i >= own.n13) break;
+        adam(s13[i], unscale(chain_sum(gs.w13, i)), as);
+        const _Float16 h = (_Float16)s13[i].p;
+        if (wv < 4) {
+          sh.w.w1t[16 * wv + 4 * g + i][r] = h;
+        } else {
+          sh.w.w3t[i][16 * (wv & 3) + r] = h;
+          sh.w.w3[16 * (wv & 3) + r][i] = h;
+        }
+      }
+    }
+    const float db = bias_sum(bs, wv, lane);
+    if (own.b >= 0) {
+      adam(sb, unscale(db), as);
+      float* const dst = (lane & 3) == 0 ? sh.w.b1 : (lane & 3) == 1 ? sh.w.b2 : sh.w.b3;
+      dst[(lane & 3) == 2 ? lane >> 2 : 4 * wv + (lane >> 2)] = sb.p;
     }
     __syncthreads();
   }
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    store_state(P, Mo, Vo, own.w2 + i, s2[i]);
+    if (i < own.n13) store_state(P, Mo, Vo, own.w13 + i, s13[i]);
+  }
+  if (own.b >= 0) store_state(P, Mo, Vo, own.b, sb);
+}
+
+// Gradient sums (scaled by S) and squared errors of the rows of passes b,
+// b + gridDim.x, ... (kTiles tiles each) into row b of part: kParams values,
+// then the loss sum.  One workgroup: the finished gradient and loss instead.
+constexpr int kPartStride = mlp::kParams + 2;
+__global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restrict__ P, const float* __restrict__ X,
+                                                            const float* __restrict__ T, int n, float S,
+                                                            float* __restrict__ part, float* __restrict__ grad,
+                                                            float* __restrict__ loss_out) {
+  __shared__ TrainShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = (int)(((int64_t)n + 15) / 16);
+  const float Btot = (float)n;
+  const int stride = (int)gridDim.x * kTiles;
+  auto load = [&](int tile) {
+    const int64_t row = (int64_t)tile * 16 + (lane & 15);
+    return load_rows(X, T, row, tile < tiles && row < n, lane);
+  };
+  int t0 = (int)blockIdx.x * kTiles;
+  TileRows next = load(t0 + wv);
+  mlp::load_weights(sh.w, P, tid, kTrainThreads);
+  __syncthreads();
+  GradSums gs;
+  BiasSums bs;
+  clear(gs, bs);
+  for (; t0 < tiles; t0 += stride) {
+    const TileRows in = next;
+    if (t0 + stride < tiles) next = load(t0 + stride + wv);
+    // whole groups of kChains tiles: the ones past the last row add zeros
+    const int nt = min(kTiles, (tiles - t0 + kChains - 1) / kChains * kChains);
+    if (wv < nt) tile_signals(sh.w, sh.t[wv], in, (int64_t)(t0 + wv) * 16 + (lane & 15) < n, S, Btot, lane);
+    __syncthreads();
+    add_tiles(sh, nt, wv, lane, gs, bs);
+    __syncthreads();  // the tiles are free again
+  }
+  const bool whole = gridDim.x == 1;
+  float* const out = whole ? grad : part + (size_t)blockIdx.x * kPartStride;
+  const float scale = whole ? S : 1.0f;
+  const Owned own = owned_params(wv, lane);
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    out[own.w2 + i] = chain_sum(gs.w2, i) / scale;
+    if (i < own.n13) out[own.w13 + i] = chain_sum(gs.w13, i) / scale;
+  }
+  const float db = bias_sum(bs, wv, lane);
+  if (own.b >= 0) out[own.b] = db / scale;
+  if (wv == 8) {
+    const float ls = sample_sum(f4{bs.loss[0], bs.loss[1], bs.loss[2], bs.loss[3]}, lane);
+    if (lane == 0) {
+      if (!whole)
+        out[mlp::kParams] = ls;
+      else if (loss_out)
+        loss_out[0] = ls / Btot;
+    }
+  }
+}
+
+// Sums of the np partial rows, in a fixed order: workgroup b takes values
+// 64 b .. 64 b + 63; its 16 waves add every 16th row each, then wave by wave.
+__global__ __launch_bounds__(1024) void k_mlp_grad_sum(const float* __restrict__ part, int np, float S, float Btot,
+                                                       float* __restrict__ grad, float* __restrict__ loss_out) {
+  __shared__ float s_sum[16][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int k = (int)blockIdx.x * 64 + lane;
+  float v = 0.f;
+  if (k <= mlp::kParams)
+    for (int r = wv; r < np; r += 16) v += part[(size_t)r * kPartStride + k];
+  s_sum[wv][lane] = v;
+  __syncthreads();
+  if (wv > 0 || k > mlp::kParams) return;
+  v = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; w++) v += s_sum[w][lane];
+  if (k < mlp::kParams)
+    grad[k] = v / S;
+  else if (loss_out)
+    loss_out[0] = v / Btot;
+}
+
+// Workgroups of a gradient over n rows: one per pass of kTiles tiles while
+// the chip has a CU for each (a workgroup's LDS fills one CU).
+constexpr int kGradMax = 256;
+int grad_groups(int32_t n) {
+  const int64_t passes = ((int64_t)n + 16 * kTiles - 1) / (16 * kTiles);
+  return (int)std::min<int64_t>(passes, kGradMax);
 }
 
 }  // namespace
@@ -303,12 +563,36 @@ int lbm_mlp_forward(const float* d_params, const float* d_x, float* d_y, int64_t
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
 }
 
+static int gradient_impl(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
+                         float* d_grad, float* d_loss, float* work, int groups, hipStream_t stream) {
+  k_mlp_grad<<<groups, kTrainThreads, 0, stream>>>(d_params, d_x, d_t, n, loss_scale, work, d_grad,
+                                                                     d_loss);
+  if (groups > 1)
+    k_mlp_grad_sum<<<(mlp::kParams + 64) / 64, 1024, 0, stream>>>(work, groups, loss_scale, (float)n, d_grad, d_loss);
+  return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
+}
+
 int lbm_mlp_gradient(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
                      float* d_grad, float* d_loss, void* hip_stream) {
   if (!d_params || !d_x || !d_t || !d_grad || n < 1 || !(loss_scale > 0)) return LBM_EINVAL;
-  k_mlp_train<<<1, 256, 0, (hipStream_t)hip_stream>>>((float*)d_params, nullptr, nullptr, d_x, d_t, n, 0, 1, 0, 0.f,
-                                                      loss_scale, d_loss, d_grad);
-  return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
+  return gradient_impl(d_params, d_x, d_t, n, loss_scale, d_grad, d_loss, nullptr, 1, (hipStream_t)hip_stream);
+}
+
+int lbm_mlp_gradient_work_size(int32_t n, size_t* bytes) {
+  if (!bytes || n < 1) return LBM_EINVAL;
+  const int g = grad_groups(n);
+  *bytes = g > 1 ? sizeof(float) * (size_t)kPartStride * g : 0;
+  return LBM_OK;
+}
+
+int lbm_mlp_gradient_in(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
+                        float* d_grad, float* d_loss, void* d_work, size_t bytes, void* hip_stream) {
+  if (!d_params || !d_x || !d_t || !d_grad || n < 1 || !(loss_scale > 0)) return LBM_EINVAL;
+  size_t need = 0;
+  (void)lbm_mlp_gradient_work_size(n, &need);
+  if (need > 0 && (!d_work || (uintptr_t)d_work % sizeof(float) || bytes < need)) return LBM_EWORKSPACE;
+  return gradient_impl(d_params, d_x, d_t, n, loss_scale, d_grad, d_loss, (float*)d_work, grad_groups(n),
+                       (hipStream_t)hip_stream);
 }
 
 int lbm_mlp_train(float* d_params, float* d_adam_m, float* d_adam_v, const float* d_x, const float* d_t, int32_t n,
@@ -317,8 +601,12 @@ int lbm_mlp_train(float* d_params, float* d_adam_m, float* d_adam_v, const float
   if (!d_params || !d_adam_m || !d_adam_v || !d_x || !d_t || n < 1 || steps < 0 || step0 < 0) return LBM_EINVAL;
   if (batch < 64 || batch % 64 || !(lr > 0) || !(loss_scale > 0)) return LBM_EINVAL;
   if (steps == 0) return LBM_OK;
-  k_mlp_train<<<1, 256, 0, (hipStream_t)hip_stream>>>(d_params, d_adam_m, d_adam_v, d_x, d_t, n, batch, steps, step0,
-                                                      lr, loss_scale, d_loss, nullptr);
+  if (batch <= 16 * kTiles)
+    k_mlp_train<true><<<1, kTrainThreads, 0, (hipStream_t)hip_stream>>>(d_params, d_adam_m, d_adam_v, d_x, d_t, n, batch,
+                                                                        steps, step0, lr, loss_scale, d_loss);
+  else
+    k_mlp_train<false><<<1, kTrainThreads, 0, (hipStream_t)hip_stream>>>(d_params, d_adam_m, d_adam_v, d_x, d_t, n,
+                                                                         batch, steps, step0, lr, loss_scale, d_loss);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
 }
 

@@ -83,6 +83,8 @@ def lib():
             "lbm_mlp_param_count": [_ip],
             "lbm_mlp_forward": [vp, vp, vp, ctypes.c_int64, vp],
             "lbm_mlp_gradient": [vp, vp, vp, ctypes.c_int32, ctypes.c_float, vp, vp, vp],
+            "lbm_mlp_gradient_work_size": [ctypes.c_int32, ctypes.POINTER(ctypes.c_size_t)],
+            "lbm_mlp_gradient_in": [vp, vp, vp, ctypes.c_int32, ctypes.c_float, vp, vp, vp, ctypes.c_size_t, vp],
             "lbm_mlp_train": [vp, vp, vp, vp, vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                               ctypes.c_float, ctypes.c_float, vp, vp],
         }
@@ -378,8 +380,14 @@ def mlp_gradient(params, x, t, loss_scale=1024.0, stream=None):
     import torch
     g = torch.empty_like(params)
     loss = torch.empty(1, dtype=torch.float32, device=params.device)
-    _check(lib().lbm_mlp_gradient(_ptr(params), _ptr(x), _ptr(t), x.shape[0], float(loss_scale), _ptr(g),
-                                  _ptr(loss), _stream(stream)), "lbm_mlp_gradient")
+    nbytes = ctypes.c_size_t(0)
+    _check(lib().lbm_mlp_gradient_work_size(x.shape[0], ctypes.byref(nbytes)), "lbm_mlp_gradient")
+    work = torch.empty(nbytes.value // 4, dtype=torch.float32, device=params.device)
+    if stream is not None:
+        work.record_stream(stream)  # allocated on the current stream, used on this one
+    _check(lib().lbm_mlp_gradient_in(_ptr(params), _ptr(x), _ptr(t), x.shape[0], float(loss_scale), _ptr(g), _ptr(loss),
+                                     ctypes.c_void_p(work.data_ptr()), nbytes.value, _stream(stream)),
+           "lbm_mlp_gradient")
     return loss, g
 
 
