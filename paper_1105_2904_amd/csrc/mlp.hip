@@ -30,38 +30,88 @@ using mlp::h4;
 
 constexpr int kWaves = 4;
 
-__global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X,
-                                                     float* __restrict__ Y, int64_t n) {
+// Bound by its vector instructions: per 16-row tile 32 tanh a lane, each an
+// exponential, a reciprocal and four ordinary operations, against 24 MFMAs and
+// 640 bytes.  So everything else is kept off the vector unit: the weight
+// operands and biases stay in registers, the tile index and with it every
+// address and bound in scalar ones, and 168 registers a lane let the products
+// land where the tanh reads them (at 128 the compiler put them in
+// accumulators, one more move each).  4,194,304 rows: 179 -> 160 us (253
+// TFLOP/s of the products).
+__global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X,
+                                                        float* __restrict__ Y, int64_t n) {
   __shared__ mlp::Weights w;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   mlp::load_weights(w, P, tid, 256);
   __syncthreads();
-  const int64_t ntiles = (n + 15) / 16;
-  const int64_t stride = (int64_t)gridDim.x * kWaves;
   const int r = lane & 15, g = lane >> 4;
-  // lane (r, g < 2) holds inputs 4g .. 4g+3 of row 16 t + r, one 16-byte load;
-  // the next tile's inputs are loaded while this one runs
-  auto load_tile = [&](int64_t t) {
-    const int64_t row = 16 * t + r;
-    f4 v = {0.f, 0.f, 0.f, 0.f};
-    if (g < 2 && row < n) v = *(const f4*)(X + row * mlp::kIn + 4 * g);
-    return v;
-  };
-  int64_t t = (int64_t)blockIdx.x * kWaves + wv;
-  f4 xnext = t < ntiles ? load_tile(t) : f4{0.f, 0.f, 0.f, 0.f};
-  for (; t < ntiles; t += stride) {
-    const f4 xc = xnext;
-    if (t + stride < ntiles) xnext = load_tile(t + stride);
-    h4 xb;
+  h4 w1[4], w2[4][4], w3[4];
+  float b1[4][4], b2[4][4];
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    w1[mt] = mlp::ld4(&w.w1t[16 * mt + r][4 * g]);
+    w3[mt] = mlp::ld4(&w.w3t[r][16 * mt + 4 * g]);
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) w2[mt][kt] = mlp::ld4(&w.w2t[16 * mt + r][16 * kt + 4 * g]);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      b1[mt][i] = w.b1[16 * mt + 4 * g + i];
+      b2[mt][i] = w.b2[16 * mt + 4 * g + i];
+    }
+  }
+  const float b30 = w.b3[0], b31 = w.b3[1];
+  // one tile: lane (r, g < 2) holds inputs 4g .. 4g+3 of row 16 t + r
+  auto tile = [&](f4 xc) {
+    h4 xb, h1[4], h2[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) xb[i] = (_Float16)xc[i];
-    h4 h1[4], h2[4];
-    f4 y;
-    mlp::forward_tile(w, xb, h1, h2, y, lane);
-    const int64_t row = 16 * t + r;
-    if (g == 0 && row < n) {
-      Y[row * mlp::kOut] = y[0] + w.b3[0];
-      Y[row * mlp::kOut + 1] = y[1] + w.b3[1];
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++) {
+      const f4 acc = mlp::mma(w1[mt], xb, zero);
+#pragma unroll
+      for (int i = 0; i < 4; i++) h1[mt][i] = (_Float16)mlp::tanh_fast(acc[i] + b1[mt][i]);
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++) {
+      f4 acc = zero;
+#pragma unroll
+      for (int kt = 0; kt < 4; kt++) acc = mlp::mma(w2[mt][kt], h1[kt], acc);
+#pragma unroll
+      for (int i = 0; i < 4; i++) h2[mt][i] = (_Float16)mlp::tanh_fast(acc[i] + b2[mt][i]);
+    }
+    f4 y = zero;
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) y = mlp::mma(w3[kt], h2[kt], y);
+    return y;
+  };
+  // whole tiles, the next one's inputs loaded while this one runs
+  const int64_t whole = n / 16;
+  const int64_t stride = (int64_t)gridDim.x * kWaves;
+  const int xoff = r * mlp::kIn + 4 * g, yoff = r * mlp::kOut;
+  int64_t t = (int64_t)blockIdx.x * kWaves + wv;
+  f4 xn = {0.f, 0.f, 0.f, 0.f};  // stays zero where g >= 2
+  if (t < whole && g < 2) xn = *(const f4*)(X + t * 16 * mlp::kIn + xoff);
+  for (; t < whole; t += stride) {
+    const f4 xc = xn;
+    if (t + stride < whole && g < 2) xn = *(const f4*)(X + (t + stride) * 16 * mlp::kIn + xoff);
+    const f4 y = tile(xc);
+    if (g == 0) {
+      float* const out = Y + t * 16 * mlp::kOut;
+      out[yoff] = y[0] + b30;
+      out[yoff + 1] = y[1] + b31;
+    }
+  }
+  // the rows past the last whole tile, in the wave whose turn it is
+  if (t == whole && n % 16 != 0) {
+    const bool has = r < (int)(n % 16);
+    f4 xc = {0.f, 0.f, 0.f, 0.f};
+    if (has && g < 2) xc = *(const f4*)(X + whole * 16 * mlp::kIn + xoff);
+    const f4 y = tile(xc);
+    if (has && g == 0) {
+      float* const out = Y + whole * 16 * mlp::kOut;
+      out[yoff] = y[0] + b30;
+      out[yoff + 1] = y[1] + b31;
     }
   }
 }
@@ -558,7 +608,12 @@ int lbm_mlp_forward(const float* d_params, const float* d_x, float* d_y, int64_t
   if (!d_params || !d_x || !d_y || n < 0) return LBM_EINVAL;
   if (n == 0) return LBM_OK;
   const int64_t tiles = (n + 15) / 16;
-  const int64_t blocks = std::min<int64_t>((tiles + kWaves - 1) / kWaves, 4096);
+  // every workgroup first stages the weights (about 5 us), so up to 2^17 tiles
+  // there are only as many as fit the chip at once (4 per CU: 200,000 rows 14
+  // us, against 18 with 2,048 and 26 with 4,096); beyond, twice as many share
+  // out the CUs' unequal speed (4,194,304 rows: 160 us, against 168 and 163)
+  const int64_t most = tiles <= (int64_t)1 << 17 ? 1024 : 2048;
+  const int64_t blocks = std::min<int64_t>((tiles + kWaves - 1) / kWaves, most);
   k_mlp_forward<<<(unsigned)blocks, 256, 0, (hipStream_t)hip_stream>>>(d_params, d_x, d_y, n);
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
 }

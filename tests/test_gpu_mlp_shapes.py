@@ -90,6 +90,21 @@ def test_training_steps(n, batch, step0):
     assert np.all(np.abs(p.cpu().numpy() - (p0 - step)) <= tol)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [5, 16, 33, 70003, (1 << 21) + 5])
+def test_forward_rows_are_independent(n):
+    """Every split of the rows over workgroups gives a row the same value."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = 3.0 * torch.rand((n, 8), device="cuda", generator=g) - 1.5
+    p = _t(_params(9))
+    y = lbm.mlp_forward(p, x)
+    parts = torch.cat([lbm.mlp_forward(p, c.contiguous()) for c in x.split(37 if n < 100 else 30011)])
+    assert torch.equal(y, parts)
+    yo, _ = omlp.forward(_params(9), x[-20:].cpu().numpy().astype(np.float64), quantize=True)
+    assert np.abs(y[-20:].cpu().numpy() - yo).max() <= 2e-3 * max(1.0, np.abs(yo).max())
+
+
 def test_gradient_workspace_is_checked_on_the_host():
     need = ctypes.c_size_t(1)
     fn, vp = lbm.lib().lbm_mlp_gradient_in, ctypes.c_void_p
