@@ -37,39 +37,48 @@ COUNTERS = os.path.join(ROOT, "profiles", "k_sweep_d3q19_256cubed_500spheres_hbm
 
 
 def pair_rows(tname, layout, nx):
-    """True when the row kernel of this storage takes two sites per lane
-    (16-bit storage, two arrays, an even row length)."""
-    return tname in ("_Float16", "bf16s") and layout == "0" and nx % 2 == 0
+    """True when the one-box kernel of this storage takes two sites per lane
+    (16-bit storage, two arrays, rows of whole cache lines above 64 sites)."""
+    return tname in ("_Float16", "bf16s") and layout == "0" and nx % 64 == 0 and nx > 64
+
+
+def streaming_rows(tname, nx):
+    """True when rows are whole 128-byte cache lines: the one-box sweeps then
+    load them streaming."""
+    return nx * {"double": 8, "float": 4}.get(tname, 2) % 128 == 0
 
 
 def sweep_geometry(box, launch, pairs=False):
     """Workgroup size and grid (threads) of the sweep launch (width, grid,
-    blocks_per_cu) on one box: the row kernel runs 256-wide workgroups over
-    ceil(nx/256) blocks per row, or with two sites per lane one 64-lane wave
-    per 128 sites of a row, four waves to a workgroup; tiles are w
-    consecutive sites of the box, one per workgroup unless a smaller
-    persistent grid is set."""
+    blocks_per_cu) on one box: the one-box kernel (width 0) runs a thread per
+    site in workgroups of 256 (64 below 32,768 sites), or with two sites per
+    lane one 64-lane wave per 128 sites of a row, four waves to a workgroup;
+    tiles are w consecutive sites of the box, one per workgroup unless a
+    smaller persistent grid is set."""
     import math
     nx, ny, nz = box
     w, g = launch["width"], launch["grid"]
     if w == 0 and pairs:
         return 256, math.ceil(math.ceil(nx / 128) * ny * nz / 4) * 256
     if w == 0:
-        return 256, math.ceil(nx / 256) * ny * nz * 256
+        wg = 64 if nx * ny * nz < 32768 else 256
+        return wg, math.ceil(nx * ny * nz / wg) * wg
     nt = math.ceil(nx * ny * nz / w)
     return w, (g if 0 < g < nt else nt) * w
 
 
 def sweep_kernel(width, q, tname, particles, layout, nx):
-    """Name of a one-box sweep kernel as the profiler lists it: the row kernel
-    (width 0; k_sweep_pairs where it takes two sites per lane) or the tile
-    kernel with streaming loads."""
+    """Name of a one-box sweep kernel as the profiler lists it: the one-box
+    kernel (width 0; k_sweep_pairs where it takes two sites per lane,
+    k_sweep_cached where rows are not whole cache lines) or the tile kernel,
+    with streaming loads or without."""
     part = "true" if particles else "false"
+    ntl = "true" if streaming_rows(tname, nx) else "false"
     if width == 0 and pair_rows(tname, layout, nx):
         return "k_sweep_pairs<%d,%s,%s>" % (q, tname, part)
     if width == 0:
-        return "k_sweep<%d,%s,%s,%s>" % (q, tname, part, layout)
-    return "k_sweep_tiles<%d,%s,%s,%s,true>" % (q, tname, part, layout)
+        return "k_sweep%s<%d,%s,%s,%s>" % ("" if ntl == "true" else "_cached", q, tname, part, layout)
+    return "k_sweep_tiles<%d,%s,%s,%s,%s>" % (q, tname, part, layout, ntl)
 
 
 def measured_traffic(kernel, workload, box, launch):

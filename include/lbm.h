@@ -218,7 +218,7 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
                  int32_t* n_particles);
 
 /* ---- launch shape, autotuning and step graphs ---------------------------
- * The sweep runs either as the one-box row kernel (width 0; one box only) or
+ * The sweep runs either as the one-box kernel (width 0; one box only) or
  * as a persistent kernel over tiles of `width` consecutive sites of one box in
  * raster order (64, 128, 256 or 512; a tile runs on across rows) with `grid`
  * workgroups (0: one per tile).  blocks_per_cu > 0 caps
@@ -227,9 +227,9 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
  * LBM_EINVAL if that exceeds what one workgroup may reserve or is below
  * 1 KiB); 0 leaves residency to the register count.  Fewer resident waves
  * can stream faster: fewer DRAM rows open at once.  With FP16/BF16 storage,
- * two arrays and an even nx the row kernel takes two sites per lane (one
- * 64-wide wave per 128 sites of a row, four waves to a workgroup).  Every
- * shape computes the same values bit for bit.  Defaults: width 0 (one box) or
+ * two arrays and nx a multiple of 64 above 64 the one-box kernel takes two
+ * sites per lane (one 64-wide wave per 128 sites of a row, four waves to a
+ * workgroup).  Every shape computes the same values bit for bit.  Defaults: width 0 (one box) or
  * 128, grid 0, no cap. */
 int lbm_set_sweep_config(lbm_ctx* ctx, int32_t width, int32_t grid, int32_t blocks_per_cu);
 int lbm_get_sweep_config(lbm_ctx* ctx, int32_t* width, int32_t* grid, int32_t* blocks_per_cu);

@@ -317,9 +317,27 @@ constexpr int kLayAB = 0, kLayAAStream = 1, kLayAASwap = 2;
 // collision with body force (eq. 1-3), and the BS substep at owned BS sites
 // (eq. 5-7) with the post-collision moments written to the owner's slot.
 // ---------------------------------------------------------------------------
+// n / d for 0 <= n < 2^31 as one 32 x 32 -> 64-bit product: m = ceil(2^sh / d)
+// with sh = 31 + ceil(log2 d), so that m < 2^32 and the product's excess over
+// n 2^sh / d, n (m d - 2^sh) / d < 2^31 d / d, stays below 2^sh / d.
+struct FastDiv {
+  uint32_t m;
+  int sh;
+};
+inline FastDiv fast_div(int d) {
+  int lg = 0;
+  while (((int64_t)1 << lg) < d) lg++;
+  return {(uint32_t)((((uint64_t)1 << (31 + lg)) + (uint64_t)d - 1) / (uint64_t)d), 31 + lg};
+}
+__host__ __device__ __forceinline__ int div_by(int n, FastDiv f) {
+  return (int)(((uint64_t)(uint32_t)n * f.m) >> f.sh);
+}
+
 template <int Q, typename C>
 struct SweepArgs {
-  int nx, ny, nz, nxb;
+  int nx, ny, nz;
+  int n;               // sites of the box
+  FastDiv by_nx, by_ny;
   C omega;   // 1 / tau
   C rho0;
   C fbt[Q];  // 3 w_i c_i . f_b
@@ -704,17 +722,50 @@ __device__ __forceinline__ void sweep_site(const T* A, T* B, const SweepArgs<Q, 
   }
 }
 
-// One box: workgroup (bx, y, z) covers kSweepBlock sites of row (y, z), with
-// streaming loads.
+// Workgroup that blockIdx.x stands for when runs of kXcdRun adjacent ones go
+// to one XCD (workgroups are dealt to the eight XCDs in turn; the ones past
+// the last whole round keep their place).
+__device__ __forceinline__ int xcd_grouped(int b, int nblocks) {
+  constexpr int R = 8 * kXcdRun;
+  return b < nblocks / R * R ? b / R * R + kXcdRun * (b % 8) + (b / 8) % kXcdRun : b;
+}
+
+// One box, blockDim.x consecutive sites of it per workgroup whatever its row
+// length.  Bound by the memory traffic of its 2q values a site.  Rows of 256
+// lanes each (one workgroup per started 256 sites of a row) left 61 % of the
+// lanes idle in a box of 100 sites to a row, and their stores began anywhere
+// in a cache line: FP64 100 x 100 x 160 sweep 103 -> 86 us, FP32 191 x 157 x
+// 173 step 271 -> 158 us, BF16 in one array 138 -> 90 us; 256^3 and 1024^2 as
+// before.
+// k_sweep, with streaming loads, where rows are whole cache lines: no two
+// workgroups then share a line, and streaming keeps dead ones out of the
+// caches (FP32 256^3 step 455 us, 479 with plain loads).  Otherwise the lines
+// at a workgroup's ends hold its neighbours' sites too: k_sweep_cached loads
+// them to stay (FP32 191-site rows 158 us, 171 streaming) and gives runs of
+// neighbours one XCD's L2 (BF16 92.3 -> 89.6 us, FP16 90.7 -> 86.9, FP32 the
+// same).
+template <int Q, typename T, bool PART, int LAY, bool NTL>
+__device__ __forceinline__ void sweep_run(int wg, const T* A, T* B, const SweepArgs<Q, typename Store<T>::C>& a,
+                                          const SiteArgs<T>& sa) {
+  const int lin = (int)((unsigned)wg * blockDim.x + threadIdx.x);
+  if (lin >= a.n) return;
+  const int row = div_by(lin, a.by_nx);
+  const int z = Q == 9 ? 0 : div_by(row, a.by_ny);
+  sweep_site<Q, T, PART, LAY, NTL>(A, B, a, sa, lin - row * a.nx, row - z * a.ny, z, a.nx, a.ny, a.nz, 0, a.fbt);
+}
 template <int Q, typename T, bool PART, int LAY>
 __global__ __launch_bounds__(kSweepBlock) void k_sweep(const T* A, T* B, SweepArgs<Q, typename Store<T>::C> a,
                                                         SiteArgs<T> sa) {
-  const int x = (int)blockIdx.x * kSweepBlock + (int)threadIdx.x;
-  if (x >= a.nx) return;
-  sweep_site<Q, T, PART, LAY, true>(A, B, a, sa, x, (int)blockIdx.y, (int)blockIdx.z, a.nx, a.ny, a.nz, 0, a.fbt);
+  sweep_run<Q, T, PART, LAY, true>((int)blockIdx.x, A, B, a, sa);
+}
+template <int Q, typename T, bool PART, int LAY>
+__global__ __launch_bounds__(kSweepBlock) void k_sweep_cached(const T* A, T* B, SweepArgs<Q, typename Store<T>::C> a,
+                                                               SiteArgs<T> sa) {
+  sweep_run<Q, T, PART, LAY, false>(xcd_grouped((int)blockIdx.x, (int)gridDim.x), A, B, a, sa);
 }
 
-// 16-bit storage, two arrays, nx even: two sites per lane.  A wave takes 128
+// 16-bit storage, two arrays, rows of whole cache lines (nx a multiple of 64)
+// longer than a wave: two sites per lane.  A wave takes 128
 // consecutive sites of a row (64 site pairs, x even), so each population is
 // one aligned 4-byte load per lane, 256 bytes per wave as FP32 moves with one
 // site per lane (2-byte loads of one site per lane stream about 10 % slower).
@@ -879,11 +930,7 @@ __global__ __launch_bounds__(kTileMax) void k_sweep_tiles(const T* A, T* B, Swee
   // L2 (64-box D2Q9 ensemble: 0.1517 -> 0.1495 ms per step tuned, +6.5 %
   // MLUPS eager).  One box keeps the hardware's order (its tiles are whole
   // rows that share no lines, and the regrouped order was 0.3 % slower).
-  int t0 = blockIdx.x;
-  if (!NTL && (int)gridDim.x == ntiles) {
-    constexpr int R = 8 * kXcdRun;
-    if (t0 < ntiles / R * R) t0 = t0 / R * R + kXcdRun * (t0 % 8) + (t0 / 8) % kXcdRun;
-  }
+  const int t0 = !NTL && (int)gridDim.x == ntiles ? xcd_grouped((int)blockIdx.x, ntiles) : (int)blockIdx.x;
   for (int t = t0; t < ntiles; t += gridDim.x) {
     const int4 tl = tiles[3 * t], tg = tiles[3 * t + 1], ti = tiles[3 * t + 2];
     const int64_t lin64 = (int64_t)tl.y + threadIdx.x;
@@ -2089,7 +2136,7 @@ struct lbm_ctx {
   int sweep_occ;            // cap on resident sweep workgroups per CU (0: none)
   int lds_cu, lds_block;    // LDS bytes per CU and the most one workgroup may reserve
   int device;               // the device the context was created on
-  bool row_ok;              // one box whose rows fit the row kernel's (x-blocks, y, z) grid
+  bool row_ok;              // one box whose ny and nz fit a launch grid: width 0 covers it
   std::vector<int> h_box;   // box of every particle
   std::vector<double> fbb;  // [nbox][3] fluid body force density
   // step graph
@@ -2134,7 +2181,7 @@ struct lbm_ctx {
 // halves with the step parity (cur), kept like the buffer index of two arrays.
 int state_layout(const lbm_ctx* c) { return c->prm.aa ? (c->cur == 0 ? kLayAAStream : kLayAASwap) : kLayAB; }
 
-// Launch shapes: widths 64..512 are the tile kernel, 0 the row kernel of one box.
+// Launch shapes: widths 64..512 are the tile kernel, 0 the one-box kernel.
 bool tile_width(int w) { return w == 64 || w == 128 || w == 256 || w == 512; }
 
 #define HIP_TRY(expr)                          \
@@ -2244,7 +2291,9 @@ SweepArgs<Q, typename Store<T>::C> sweep_args(const lbm_ctx* c) {
   a.nx = c->G.nx;
   a.ny = c->G.ny;
   a.nz = c->G.nz;
-  a.nxb = (c->G.nx + kSweepBlock - 1) / kSweepBlock;
+  a.n = (int)c->G.N;
+  a.by_nx = fast_div(c->G.nx);
+  a.by_ny = fast_div(c->G.ny);
   a.omega = (C)(1.0 / c->prm.tau);
   a.rho0 = (C)c->prm.rho0;
   a.walls = c->prm.walls;
@@ -2276,9 +2325,14 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
   const T* A = (const T*)c->f[c->cur];
   T* B = (T*)c->f[1 - c->cur];  // the same array under the AA pattern
   const SiteArgs<T> sa = site_args<Q, T>(c);
+  const bool lines = (size_t)a.nx * sizeof(T) % 128 == 0;  // rows are whole cache lines
   if (w == 0) {
     if constexpr (sizeof(T) == 2 && LAY == kLayAB) {
-      if (a.nx % 2 == 0) {  // two sites per lane: one wave per 128 sites of a row
+      // two sites per lane, one wave per 128 sites of a row, while rows are
+      // whole cache lines and fill a wave (FP16, 5.2 M sites, step by row
+      // length, against one site per lane: 128 86.7 / 90.4 us, 192 88.1 / 93.0,
+      // 320 89.1 / 94.0; but 64 106.3 / 85.5, 250 118.7 / 91.2)
+      if (lines && a.nx > 64) {
         const int64_t waves = (int64_t)((a.nx + kPairRow - 1) / kPairRow) * c->G.ny * c->G.nz;
         const unsigned g = (unsigned)((waves + kSweepBlock / 64 - 1) / (kSweepBlock / 64));
         if (c->np > 0)
@@ -2289,23 +2343,31 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
         return LBM_OK;
       }
     }
-    const dim3 grid3((unsigned)a.nxb, (unsigned)c->G.ny, (unsigned)c->G.nz);
-    if (c->np > 0)
-      k_sweep<Q, T, true, LAY><<<grid3, kSweepBlock, lds, c->stream>>>(A, B, a, sa);
+    // a box of fewer than 128 workgroups of 256 spreads over more CUs in waves
+    // of one (64^2 step 15.2 -> 14.7 us); larger ones share lines less with
+    // wide workgroups (191-site rows FP32 158 us, 169 with 64 threads)
+    const int block = a.n < 128 * kSweepBlock ? 64 : kSweepBlock;
+    const unsigned g = blocks_for(a.n, block);
+    if (c->np > 0 && lines)
+      k_sweep<Q, T, true, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
+    else if (c->np > 0)
+      k_sweep_cached<Q, T, true, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
+    else if (lines)
+      k_sweep<Q, T, false, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
     else
-      k_sweep<Q, T, false, LAY><<<grid3, kSweepBlock, lds, c->stream>>>(A, B, a, sa);
+      k_sweep_cached<Q, T, false, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
   } else {
     const int64_t nt = c->ntiles;
     const unsigned g = (unsigned)(grid > 0 && grid < nt ? grid : nt);
-    // streaming loads for one box, cached ones for an ensemble
-    const bool one = c->nbox == 1;
-    if (c->np > 0 && one)
+    // streaming loads for one box of whole-line rows, cached ones otherwise (as k_sweep)
+    const bool ntl = c->nbox == 1 && lines;
+    if (c->np > 0 && ntl)
       k_sweep_tiles<Q, T, true, LAY, true><<<g, w, lds, c->stream>>>(A, B, a, sa, c->d_tiles, (int)nt,
                                                                       (const C*)c->d_fbt);
     else if (c->np > 0)
       k_sweep_tiles<Q, T, true, LAY, false><<<g, w, lds, c->stream>>>(A, B, a, sa, c->d_tiles, (int)nt,
                                                                        (const C*)c->d_fbt);
-    else if (one)
+    else if (ntl)
       k_sweep_tiles<Q, T, false, LAY, true><<<g, w, lds, c->stream>>>(A, B, a, sa, c->d_tiles, (int)nt,
                                                                        (const C*)c->d_fbt);
     else
@@ -2658,7 +2720,7 @@ static int create_impl(const lbm_params* prm, int nbox, const int32_t* dims, voi
     c->row_ok = nbox == 1 && dims[1] <= gy && dims[2] <= gz;
     c->device = dev;
   }
-  // one box: the row kernel; an ensemble: tiles of 128 sites, one workgroup each
+  // one box: the one-box kernel; an ensemble: tiles of 128 sites, one workgroup each
   c->sweep_w = c->row_ok ? 0 : 128;
   c->sweep_grid = 0;
   c->sweep_occ = 0;
@@ -3092,7 +3154,7 @@ int lbm_set_graph(lbm_ctx* c, int32_t steps_per_graph) {
 int lbm_set_sweep_config(lbm_ctx* c, int32_t width, int32_t grid, int32_t blocks_per_cu) {
   if (!c || grid < 0 || !occ_ok(c, blocks_per_cu)) return LBM_EINVAL;
   if (width != 0 && !tile_width(width)) return LBM_EINVAL;
-  if (width == 0 && !c->row_ok) return LBM_EINVAL;  // the row kernel covers one box
+  if (width == 0 && !c->row_ok) return LBM_EINVAL;  // width 0 covers one box
   if (tile_width(width)) {
     const int rc = build_tiles(c, width);
     if (rc != LBM_OK) return rc;
