@@ -40,13 +40,17 @@
 // momentum differences behind the particle forces survive FP32 storage.
 #include <hip/hip_runtime.h>
 
+#include <sched.h>
+
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -1871,19 +1875,20 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
 // Moments of sites s0 .. s0 + cnt - 1 of box G (box-local indices).
 template <int Q, typename T>
 __global__ void k_moments(const T* __restrict__ A, double* __restrict__ rho, double* __restrict__ u,
-                          Geo G, double rho0, int64_t s0, int64_t cnt, int lay) {
+                          Geo G, FastDiv by_nx, FastDiv by_ny, double rho0, int64_t s0, int64_t cnt, int lay) {
   using L = Lattice<Q>;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= cnt) return;
-  const int64_t s = s0 + idx;
-  const int x = (int)(s % G.nx), y = (int)((s / G.nx) % G.ny), z = (int)(s / ((int64_t)G.nx * G.ny));
+  const int s = (int)(s0 + idx);
+  const int row = div_by(s, by_nx), z = div_by(row, by_ny);
+  const int x = s - row * G.nx, y = row - z * G.ny;
   double drho = 0, j[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < Q; i++) {
     // f_i arriving at x (the three state layouts)
     const bool here = lay == kLayAAStream;
-    const int sx = here ? x : wrap(x - L::cx(i), G.nx), sy = here ? y : wrap(y - L::cy(i), G.ny),
-              sz = here ? z : wrap(z - L::cz(i), G.nz);
+    const int sx = here ? x : wrap1(x - L::cx(i), G.nx), sy = here ? y : wrap1(y - L::cy(i), G.ny),
+              sz = here ? z : wrap1(z - L::cz(i), G.nz);
     const int plane = lay == kLayAASwap ? opposite<Q>(i) : i;
     const double g = (double)pop_ld<Q, T>(A + pop_elem(Q, plane, site_of(G, sx, sy, sz)), i);
     drho += g;
@@ -1894,6 +1899,33 @@ __global__ void k_moments(const T* __restrict__ A, double* __restrict__ rho, dou
   const double r = rho0 + drho;
   rho[idx] = r;
   for (int a = 0; a < 3; a++) u[3 * idx + a] = j[a] / r;
+}
+
+// Owner particle of sites s0 .. s0 + cnt - 1 from the owner map (-1: none).
+__global__ void k_owners(const int* __restrict__ own, const int* __restrict__ pid, int* __restrict__ owner, int64_t s0,
+                         int64_t cnt) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= cnt) return;
+  const int o = own[s0 + idx];
+  owner[idx] = o == kEmpty ? -1 : pid[o >> 1];
+}
+
+// The status word and the particles' F, T, x, u, omega (3n values each) into
+// pinned host memory: kHostHead bytes, then the arrays.  One launch and one
+// wait, where five copies to pageable memory and the status word's took 90 us.
+constexpr size_t kHostHead = 64;
+constexpr size_t kFieldBlock = (size_t)4 << 20;  // pinned block of a field read-out
+constexpr int kHostParticles = 16384;  // most particles read out that way (2 MB)
+__global__ void k_read_particles(DevParticles P, const int* __restrict__ status, int n3, char* __restrict__ host) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < 4) ((int*)host)[i] = status[i];
+  if (i >= n3) return;
+  double* const d = (double*)(host + kHostHead);
+  d[i] = P.F[i];
+  d[(size_t)n3 + i] = P.T[i];
+  d[2 * (size_t)n3 + i] = P.x[i];
+  d[3 * (size_t)n3 + i] = P.u[i];
+  d[4 * (size_t)n3 + i] = P.om[i];
 }
 
 // B_i(s) = A_i(s - dir * c_i) over the sites of box G: dir = +1 pulls
@@ -2117,6 +2149,181 @@ int check_params(const lbm_params* p) {
 }  // namespace
 
 // ---------------------------------------------------------------------------
+// Pinned host memory for read-outs.  Pinning costs more than the read-outs
+// it speeds up (0.2 ms and more), so blocks go back to a pool that any context
+// may take them from, and all of it to the system with the last context.
+// Blocks up to kSmallBlock are pieces of slabs, as many as contexts ever
+// needed at once; of larger ones the pool keeps at most kPoolBlocks and
+// kPoolBytes.  A block has one user at a time.
+// ---------------------------------------------------------------------------
+struct HostBlock {
+  void* p;
+  size_t bytes;
+};
+
+namespace {
+
+constexpr size_t kSmallBlock = (size_t)64 << 10;
+constexpr int kSlabPieces = 16;
+constexpr int kPoolBlocks = 16;
+constexpr size_t kPoolBytes = (size_t)64 << 20;
+struct Piece {  // a free piece of a slab
+  Piece* next;
+};
+struct Slab {
+  Slab* next;
+  void* p;
+};
+std::mutex g_pool_mu;
+Piece* g_pieces = nullptr;
+Slab* g_slabs = nullptr;
+HostBlock g_pool[kPoolBlocks];
+int g_pool_n = 0;
+size_t g_pool_bytes = 0;
+int g_pool_users = 0;  // live contexts
+
+void* pin(size_t bytes) {
+  void* p = nullptr;
+  if (hipHostMalloc(&p, bytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+// A block of at least `bytes`, empty if there is none to be had.
+HostBlock host_take(size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  if (bytes <= kSmallBlock) {
+    if (!g_pieces) {
+      Slab* const slab = new (std::nothrow) Slab{g_slabs, pin(kSmallBlock * kSlabPieces)};
+      if (!slab || !slab->p) {
+        delete slab;
+        return HostBlock{nullptr, 0};
+      }
+      g_slabs = slab;
+      for (int k = 0; k < kSlabPieces; k++)
+        g_pieces = new ((char*)slab->p + k * kSmallBlock) Piece{g_pieces};
+    }
+    Piece* const piece = g_pieces;
+    g_pieces = piece->next;
+    return HostBlock{piece, kSmallBlock};
+  }
+  int best = -1;
+  for (int k = 0; k < g_pool_n; k++)
+    if (g_pool[k].bytes >= bytes && g_pool[k].bytes <= 4 * bytes && (best < 0 || g_pool[k].bytes < g_pool[best].bytes))
+      best = k;
+  if (best >= 0) {
+    const HostBlock b = g_pool[best];
+    g_pool[best] = g_pool[--g_pool_n];
+    g_pool_bytes -= b.bytes;
+    return b;
+  }
+  void* const p = pin(bytes);
+  return HostBlock{p, p ? bytes : 0};
+}
+void host_give(HostBlock b) {
+  if (!b.p) return;
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  if (b.bytes == kSmallBlock) {
+    g_pieces = new (b.p) Piece{g_pieces};
+  } else if (g_pool_n < kPoolBlocks && g_pool_bytes + b.bytes <= kPoolBytes) {
+    g_pool[g_pool_n++] = b;
+    g_pool_bytes += b.bytes;
+  } else {
+    (void)hipHostFree(b.p);
+  }
+}
+void pool_enter() {
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  g_pool_users++;
+}
+void pool_leave() {
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  if (--g_pool_users > 0) return;
+  while (g_pool_n > 0) (void)hipHostFree(g_pool[--g_pool_n].p);
+  g_pool_bytes = 0;
+  g_pieces = nullptr;
+  while (g_slabs) {
+    Slab* const slab = g_slabs;
+    g_slabs = slab->next;
+    (void)hipHostFree(slab->p);
+    delete slab;
+  }
+}
+
+// Copies from a pinned block to the caller's arrays, shared by a few threads:
+// one thread moves about 5 GB/s into pages that are touched for the first
+// time, the link ten times that.  The threads live as long as the object and
+// spin between copies.  No more than one thread (the caller's) if none can be
+// started.
+class CopyTeam {
+ public:
+  struct Part {
+    char* dst;
+    const char* src;
+    size_t bytes;
+  };
+  explicit CopyTeam(size_t total) noexcept {
+    cpu_set_t set;
+    int cpus = 1;
+    if (sched_getaffinity(0, sizeof(set), &set) == 0) cpus = CPU_COUNT(&set);
+    const int want = total < ((size_t)1 << 20) ? 1 : std::min(kMost, std::max(1, cpus / 2));
+    for (int k = 1; k < want; k++) {
+      try {
+        th_[n_ - 1] = std::thread([this, k] { work(k); });
+      } catch (...) {
+        break;
+      }
+      n_++;
+    }
+  }
+  ~CopyTeam() {
+    quit_.store(true, std::memory_order_release);
+    for (int k = 0; k + 1 < n_; k++) th_[k].join();
+  }
+  void copy(const Part* parts, int count) noexcept {
+    parts_ = parts;
+    count_ = count;
+    left_.store(n_ - 1, std::memory_order_relaxed);
+    turn_.fetch_add(1, std::memory_order_release);
+    stripe(0);
+    while (left_.load(std::memory_order_acquire) > 0) std::this_thread::yield();
+  }
+
+ private:
+  static constexpr int kMost = 8;
+  // thread k's share of every part, split at page boundaries of the target
+  void stripe(int k) const noexcept {
+    const int n = n_;  // written before the first turn
+    for (int j = 0; j < count_; j++) {
+      const Part& p = parts_[j];
+      const size_t a = p.bytes * (size_t)k / (size_t)n / 4096 * 4096;
+      const size_t b = k + 1 == n ? p.bytes : p.bytes * (size_t)(k + 1) / (size_t)n / 4096 * 4096;
+      if (b > a) std::memcpy(p.dst + a, p.src + a, b - a);
+    }
+  }
+  void work(int k) noexcept {
+    int seen = 0;
+    for (;;) {
+      while (turn_.load(std::memory_order_acquire) == seen) {
+        if (quit_.load(std::memory_order_acquire)) return;
+        std::this_thread::yield();
+      }
+      seen++;
+      stripe(k);
+      left_.fetch_sub(1, std::memory_order_release);
+    }
+  }
+  std::thread th_[kMost - 1];
+  int n_ = 1;
+  std::atomic<int> turn_{0}, left_{0};
+  std::atomic<bool> quit_{false};
+  const Part* parts_ = nullptr;
+  int count_ = 0;
+};
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
 // Context
 // ---------------------------------------------------------------------------
 struct lbm_ctx {
@@ -2175,6 +2382,7 @@ struct lbm_ctx {
   bool failed;  // a HIP error left the device state part-way through an update
   std::vector<hipEvent_t> ev;
   size_t ev_used;
+  HostBlock host;  // pinned: the status word and the particle read-outs (may be empty)
 };
 
 // Layout of the state between steps: the AA pattern alternates its two
@@ -2444,8 +2652,9 @@ int launch_step(lbm_ctx* c) {
 
 template <int Q, typename T>
 int launch_moments(lbm_ctx* c, int box, double* d_rho, double* d_u, int64_t s0, int64_t cnt) {
-  k_moments<Q, T><<<blocks_for(cnt), 256, 0, c->stream>>>((const T*)c->f[c->cur], d_rho, d_u, c->boxes[box],
-                                                          c->prm.rho0, s0, cnt, state_layout(c));
+  const Geo& g = c->boxes[box];
+  k_moments<Q, T><<<blocks_for(cnt), 256, 0, c->stream>>>((const T*)c->f[c->cur], d_rho, d_u, g, fast_div(g.nx),
+                                                          fast_div(g.ny), c->prm.rho0, s0, cnt, state_layout(c));
   HIP_TRY(hipGetLastError());
   return LBM_OK;
 }
@@ -2538,19 +2747,34 @@ int refresh_owner_map(lbm_ctx* c) {
   return LBM_OK;
 }
 
+// The call's result for the device status word st; a reported one is cleared.
+int report_status(lbm_ctx* c, int st) {
+  if (st == 0) return LBM_OK;
+  const int zero[4] = {0, 0, 0, 0};
+  HIP_TRY(hipMemcpyAsync(c->status, zero, sizeof(zero), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  if (st & kStatusRecord) return LBM_ESTATE;
+  if (st & kStatusCollision) return LBM_ECOLLISION;
+  if (st & kStatusClosure) return LBM_ECAPACITY;
+  return LBM_OK;
+}
+
+// Waits for the stream and reports the status word, with np particles' state
+// (0: the word alone) in the context's pinned block if it has one.
+int read_particles(lbm_ctx* c, int np) {
+  const int n3 = 3 * np;
+  k_read_particles<<<blocks_for(std::max(n3, 4)), 256, 0, c->stream>>>(c->P, c->status, n3, (char*)c->host.p);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  return report_status(c, *(volatile int*)c->host.p);
+}
+
 int check_status(lbm_ctx* c) {
+  if (c->host.p) return read_particles(c, 0);
   int st[4];
   HIP_TRY(hipMemcpyAsync(st, c->status, sizeof(st), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (st[0] != 0) {
-    const int zero[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(c->status, zero, sizeof(zero), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (st[0] & kStatusRecord) return LBM_ESTATE;
-    if (st[0] & kStatusCollision) return LBM_ECOLLISION;
-    if (st[0] & kStatusClosure) return LBM_ECAPACITY;
-  }
-  return LBM_OK;
+  return report_status(c, st[0]);
 }
 
 // Box table and per-box forcing terms 3 w_i c_i . f_b to the device.
@@ -2785,6 +3009,12 @@ static int create_impl(const lbm_params* prm, int nbox, const int32_t* dims, voi
     delete c;
     return LBM_EHIP;
   }
+  // the particle read-outs of up to kHostParticles particles; without it they
+  // are copied array by array
+  pool_enter();
+  c->host = prm->max_particles <= kHostParticles
+                ? host_take(kHostHead + 15 * sizeof(double) * (size_t)std::max(prm->max_particles, 64))
+                : HostBlock{nullptr, 0};
   *out = c;
   return LBM_OK;
 }
@@ -2809,6 +3039,8 @@ int lbm_destroy(lbm_ctx* c) {
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   drop_graph(c);
   if (c->cap) (void)hipStreamDestroy(c->cap);
+  host_give(c->host);
+  pool_leave();
   delete c;
   return LBM_OK;
 }
@@ -3395,6 +3627,13 @@ int lbm_forces(lbm_ctx* c, double* F, double* T, double* x, double* u, double* o
   if (!c) return LBM_EINVAL;
   if (c->failed) return LBM_EHIP;
   const size_t b = sizeof(double) * 3 * c->np;
+  if (c->np > 0 && c->host.p) {
+    const int rc = read_particles(c, c->np);
+    double* const to[5] = {F, T, x, u, omega};
+    for (int k = 0; k < 5; k++)
+      if (to[k]) std::memcpy(to[k], (const char*)c->host.p + kHostHead + k * b, b);
+    return rc;
+  }
   if (c->np > 0) {
     if (F) HIP_TRY(hipMemcpyAsync(F, c->P.F, b, hipMemcpyDeviceToHost, c->stream));
     if (T) HIP_TRY(hipMemcpyAsync(T, c->P.T, b, hipMemcpyDeviceToHost, c->stream));
@@ -3408,35 +3647,90 @@ int lbm_forces(lbm_ctx* c, double* F, double* T, double* x, double* u, double* o
 int lbm_fields(lbm_ctx* c, double* rho, double* u, int32_t* owner) {
   if (!c) return LBM_EINVAL;
   if (c->failed) return LBM_EHIP;
-  if (rho || u) {
-    // two arrays: the idle one stages the moments; AA: the staging area
-    const size_t stage = c->prm.aa ? 4 * sizeof(double) * (size_t)std::min<int64_t>(c->NT, (int64_t)1 << 20)
-                                   : (size_t)c->q * c->PS * store_size(c->prm.storage);
-    const int64_t chunk = (int64_t)(stage / (4 * sizeof(double)));
-    double* d_rho = c->prm.aa ? (double*)(c->ws + c->L.stage) : (double*)c->f[1 - c->cur];
-    double* d_u = d_rho + chunk;
-    for (int b = 0; b < c->nbox; b++) {
-      const Geo& g = c->boxes[b];
-      for (int64_t s0 = 0; s0 < g.N; s0 += chunk) {
-        const int64_t cnt = std::min<int64_t>(chunk, g.N - s0);
-        const int rc = DISPATCH(c, launch_moments, c, b, d_rho, d_u, s0, cnt);
-        if (rc != LBM_OK) return rc;
-        if (rho)
-          HIP_TRY(hipMemcpyAsync(rho + g.off + s0, d_rho, sizeof(double) * cnt, hipMemcpyDeviceToHost, c->stream));
-        if (u)
-          HIP_TRY(hipMemcpyAsync(u + 3 * (g.off + s0), d_u, sizeof(double) * 3 * cnt, hipMemcpyDeviceToHost,
-                                 c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-      }
-    }
-  }
+  if (!rho && !u && !owner) return check_status(c);
   if (owner) {
     const int orc = refresh_owner_map(c);
     if (orc != LBM_OK) return orc;
-    std::vector<int> m(c->NT);
-    HIP_TRY(hipMemcpyAsync(m.data(), c->own, sizeof(int) * c->NT, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    for (int64_t s = 0; s < c->NT; s++) owner[s] = m[s] == kEmpty ? -1 : c->h_pid[m[s] >> 1];
+  }
+  // A chunk of sites, of any boxes, at a time: its density, velocity and owner
+  // side by side in device memory (two arrays: the idle one; AA: the staging
+  // area), one copy to a pinned block, and from there to the caller's arrays
+  // while the next chunk is on its way.  Without pinned blocks the copies go
+  // straight to the caller's arrays.
+  constexpr size_t kSite = 8 + 24 + 4;
+  const size_t aa_stage = 4 * sizeof(double) * (size_t)std::min<int64_t>(c->NT, (int64_t)1 << 20);
+  const size_t stage = c->prm.aa ? (aa_stage + kAlign - 1) / kAlign * kAlign  // as laid out
+                                 : (size_t)c->q * c->PS * store_size(c->prm.storage);
+  char* const d = c->prm.aa ? c->ws + c->L.stage : (char*)c->f[1 - c->cur];
+  const int64_t chunk =
+      std::min<int64_t>({(int64_t)(stage / kSite), (int64_t)(kFieldBlock / kSite), c->NT});
+  const int64_t nchunk = (c->NT + chunk - 1) / chunk;
+  struct Blocks {
+    HostBlock b[2] = {{nullptr, 0}, {nullptr, 0}};
+    hipEvent_t done[2] = {nullptr, nullptr};
+    ~Blocks() {
+      for (int k = 0; k < 2; k++) {
+        host_give(b[k]);
+        if (done[k]) (void)hipEventDestroy(done[k]);
+      }
+    }
+  } hb;
+  bool pinned = true;
+  for (int k = 0; k < (nchunk > 1 ? 2 : 1) && pinned; k++) {
+    hb.b[k] = host_take(kSite * (size_t)chunk);
+    pinned = hb.b[k].p && hipEventCreateWithFlags(&hb.done[k], hipEventDisableTiming) == hipSuccess;
+  }
+  CopyTeam team(pinned ? kSite * (size_t)c->NT : 0);
+  auto fetch = [&](int64_t k) -> int {  // chunk k into block k % 2
+    const int64_t a = k * chunk, n = std::min<int64_t>(chunk, c->NT - a);
+    double* const d_rho = (double*)d;
+    double* const d_u = d_rho + n;
+    int* const d_own = (int*)(d_u + 3 * n);
+    if (rho || u)
+      for (int b = 0; b < c->nbox; b++) {
+        const Geo& g = c->boxes[b];
+        const int64_t s0 = std::max<int64_t>(a, g.off), s1 = std::min<int64_t>(a + n, g.off + g.N);
+        if (s1 <= s0) continue;
+        const int rc = DISPATCH(c, launch_moments, c, b, d_rho + (s0 - a), d_u + 3 * (s0 - a), s0 - g.off, s1 - s0);
+        if (rc != LBM_OK) return rc;
+      }
+    if (owner) {
+      k_owners<<<blocks_for(n), 256, 0, c->stream>>>(c->own, c->E.pid, d_own, a, n);
+      HIP_TRY(hipGetLastError());
+    }
+    if (!pinned) {
+      if (rho) HIP_TRY(hipMemcpyAsync(rho + a, d_rho, 8 * n, hipMemcpyDeviceToHost, c->stream));
+      if (u) HIP_TRY(hipMemcpyAsync(u + 3 * a, d_u, 24 * n, hipMemcpyDeviceToHost, c->stream));
+      if (owner) HIP_TRY(hipMemcpyAsync(owner + a, d_own, 4 * n, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+      return LBM_OK;
+    }
+    const size_t from = rho ? 0 : (u ? 8 * n : 32 * n), to = owner ? 36 * n : (u ? 32 * n : 8 * n);
+    HIP_TRY(hipMemcpyAsync((char*)hb.b[k % 2].p + from, d + from, to - from, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipEventRecord(hb.done[k % 2], c->stream));
+    return LBM_OK;
+  };
+  auto hand_out = [&](int64_t k) -> int {
+    const int64_t a = k * chunk, n = std::min<int64_t>(chunk, c->NT - a);
+    HIP_TRY(hipEventSynchronize(hb.done[k % 2]));
+    const char* const h = (const char*)hb.b[k % 2].p;
+    CopyTeam::Part part[3];
+    int m = 0;
+    if (rho) part[m++] = {(char*)(rho + a), h, 8 * (size_t)n};
+    if (u) part[m++] = {(char*)(u + 3 * a), h + 8 * n, 24 * (size_t)n};
+    if (owner) part[m++] = {(char*)(owner + a), h + 32 * n, 4 * (size_t)n};
+    team.copy(part, m);
+    return LBM_OK;
+  };
+  int rc = LBM_OK;
+  for (int64_t k = 0; k < nchunk && rc == LBM_OK; k++) {
+    rc = fetch(k);
+    if (rc == LBM_OK && pinned && k > 0) rc = hand_out(k - 1);
+  }
+  if (rc == LBM_OK && pinned) rc = hand_out(nchunk - 1);
+  if (rc != LBM_OK) {
+    (void)hipStreamSynchronize(c->stream);  // no copy into a block after it is given back
+    return rc;
   }
   return check_status(c);
 }

@@ -296,14 +296,15 @@ class Simulation:
 
     def forces(self):
         n = self.n_particles
-        F, T, x, u, om = (np.zeros((n, 3)) for _ in range(5))
-        _check(lib().lbm_forces(self.ctx, _d(F), _d(T), _d(x), _d(u), _d(om)), "lbm_forces")
-        return F, T, x, u, om
+        out = np.zeros((5, n, 3))
+        at, size = out.ctypes.data, 24 * n
+        _check(lib().lbm_forces(self.ctx, *(ctypes.cast(at + k * size, _dp) for k in range(5))), "lbm_forces")
+        return tuple(out)  # F, T, x, u, omega
 
     def fields(self):
-        rho = np.zeros(self.N)
-        u = np.zeros((self.N, 3))
-        own = np.zeros(self.N, dtype=np.int32)
+        rho = np.empty(self.N)
+        u = np.empty((self.N, 3))
+        own = np.empty(self.N, dtype=np.int32)
         _check(lib().lbm_fields(self.ctx, _d(rho), _d(u), own.ctypes.data_as(_ip)), "lbm_fields")
         if len(self.dims) > 1:
             return rho, u, own  # sites of every box, box after box
