@@ -29,6 +29,8 @@
 //              rigid-body velocity u_p + omega x r of its next BS substep
 //              (eq. 5) and the owner entry; a BS entry whose site is held by
 //              another particle or a wall marks its slot unowned instead.
+// Boxes of a few particles take the last three in one launch, one workgroup per
+// box (k_box).
 // Boxes of so many large balls that the lists of particles that may share a
 // site could overflow keep an owner map instead: reduce releases
 // it, a stamp launch rebuilds it at the new shifts (eq. 14-15) and prepare
@@ -953,10 +955,42 @@ __global__ __launch_bounds__(kTileMax) void k_sweep_tiles(const T* A, T* B, Swee
 // ---------------------------------------------------------------------------
 // Deterministic sums: butterfly within the 64-wide wave, then waves in order.
 // ---------------------------------------------------------------------------
+// The value of lane ^ OFF (8, 4, 2 or 1), moved between lanes in the vector
+// unit: a rotation of a 16-lane row by 8, a mirrored half row with its quads
+// reversed, and quad permutations.  Through LDS (shuffles) the sums of a
+// particle took about 0.7 us more (1024^2 with 200 disks: step 31.4 -> 30.6 us).
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (OFF == 8) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xf, 0xf, false);
+  } else if constexpr (OFF == 4) {
+    const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141 /* row_half_mirror */, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1b /* quad_perm:[3,2,1,0] */, 0xf, 0xf, false);
+  } else {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, OFF == 2 ? 0x4e /* quad_perm:[2,3,0,1] */
+                                                                     : 0xb1 /* quad_perm:[1,0,3,2] */,
+                                                 0xf, 0xf, false);
+  }
+}
+// v + (the same of lane ^ OFF); half-waves and 16-lane rows by a swap.
+template <int OFF>
+__device__ __forceinline__ double add_xor(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  if constexpr (OFF == 32 || OFF == 16) {
+    // a swap of the value with itself yields both addends in every lane
+    const auto lo = OFF == 32 ? __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false)
+                              : __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi = OFF == 32 ? __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false)
+                              : __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+  } else {
+    const uint32_t lo = lane_xor<OFF>((uint32_t)b), hi = lane_xor<OFF>((uint32_t)(b >> 32));
+    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  }
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  return add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(add_xor<16>(add_xor<32>(v))))));
 }
 
 // Exclusive prefix sum of c over a workgroup of NT threads: a shuffle scan in
@@ -1011,6 +1045,81 @@ struct PartView {
   __device__ __forceinline__ double R(int p) const { return r[p - p0]; }
 };
 
+// Newton-Euler (eq. 10-11): the fluid's momentum change dp, dl, the closure's
+// force fc and the buoyancy-corrected weight fe change u and om; returns the
+// squared speed.
+__device__ __forceinline__ double accelerate(double m, double I, const double (&dp)[3], const double (&dl)[3],
+                                             const double (&fc)[3], const double (&fe)[3], double (&u)[3],
+                                             double (&om)[3]) {
+  double v2 = 0;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    if (!isinf(m)) u[a] = u[a] + (fe[a] - dp[a] + fc[a]) / m;
+    if (!isinf(I)) om[a] = om[a] - dl[a] / I;
+    v2 += u[a] * u[a];
+  }
+  return v2;
+}
+
+// Hard-core collision of a candidate pair (eq. 16-19) at the velocities the
+// pairs before it left; vseen: the largest speed so far.
+__device__ __forceinline__ void collide_pair(const PartView& V, int i, int j, const int (&L)[3], int dim,
+                                             double& vseen) {
+  const double mi = V.M(i), mj = V.M(j), ri = V.R(i), rj = V.R(j);
+  const bool infA = isinf(mi), infB = isinf(mj);
+  if (infA && infB) return;
+  double d[3], dd = 0;
+  for (int a = 0; a < 3; a++) {
+    d[a] = (V.X(j, a) + V.U(j, a)) - (V.X(i, a) + V.U(i, a));
+    if (a < dim) d[a] = d[a] - L[a] * floor(d[a] / L[a] + 0.5);
+    dd += d[a] * d[a];
+  }
+  const double dist = sqrt(dd);
+  if (dist > ri + rj || dist == 0.0) return;
+  double n[3], vn = 0;
+  for (int a = 0; a < 3; a++) {
+    n[a] = d[a] / dist;
+    vn += (V.U(j, a) - V.U(i, a)) * n[a];
+  }
+  if (!(vn < 0.0)) return;
+  double W[3];
+  for (int a = 0; a < 3; a++) {
+    if (infA)
+      W[a] = V.U(i, a);
+    else if (infB)
+      W[a] = V.U(j, a);
+    else
+      W[a] = (mi * V.U(i, a) + mj * V.U(j, a)) / (mi + mj);
+  }
+  const int who[2] = {i, j};
+  for (int t2 = 0; t2 < 2; t2++) {
+    const int q = who[t2];
+    double wvv[3], wn = 0, v2 = 0;
+    for (int a = 0; a < 3; a++) {
+      wvv[a] = V.U(q, a) - W[a];
+      wn += wvv[a] * n[a];
+    }
+    for (int a = 0; a < 3; a++) {
+      const double u = W[a] + (wvv[a] - 2.0 * wn * n[a]);
+      V.U(q, a) = u;
+      v2 += u * u;
+    }
+    vseen = fmax(vseen, sqrt(v2));
+  }
+}
+
+// Contact with a wall after the pairs: the normal velocity reverses when the
+// predicted surface reaches the BS layer while approaching.
+__device__ __forceinline__ void bounce_walls(const Geo& G, const int (&L)[3], int dim, double m, double r,
+                                             const double (&x)[3], double (&u)[3]) {
+  if (!G.walls || isinf(m)) return;
+  for (int a = 0; a < dim; a++) {
+    if (!(G.walls & (1 << a))) continue;
+    const double xp = x[a] + u[a];
+    if ((xp - r <= 1.0 && u[a] < 0.0) || (xp + r >= (double)(L[a] - 2) && u[a] > 0.0)) u[a] = -u[a];
+  }
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) void k_particles(DevParticles P, int dim, Boxes BX, int* status) {
   __shared__ double s_x[3 * kStageParticles], s_u[3 * kStageParticles], s_m[kStageParticles], s_r[kStageParticles];
@@ -1059,13 +1168,7 @@ __global__ __launch_bounds__(NT) void k_particles(DevParticles P, int dim, Boxes
       }
       cnr = P.cand_n[p];
     }
-    double v2 = 0;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-      if (!isinf(m)) u[a] = u[a] + (fe[a] - dp[a] + fc[a]) / m;
-      if (!isinf(I)) om[a] = om[a] - dl[a] / I;
-      v2 += u[a] * u[a];
-    }
+    const double v2 = accelerate(m, I, dp, dl, fc, fe, u, om);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
       P.F[3 * p + a] = -dp[a] + fc[a];
@@ -1114,48 +1217,7 @@ __global__ __launch_bounds__(NT) void k_particles(DevParticles P, int dim, Boxes
                               : PartView{P.x, P.u, P.m, P.rad, 1, 3, 0};
     for (int k = 0; k < total; k++) {
       const int2 pr = k < kStagePairs ? s_pairs[k] : gpairs[k];
-      const int i = pr.x, j = pr.y;
-      const double mi = V.M(i), mj = V.M(j), ri = V.R(i), rj = V.R(j);
-      const bool infA = isinf(mi), infB = isinf(mj);
-      if (infA && infB) continue;
-      double d[3], dd = 0;
-      for (int a = 0; a < 3; a++) {
-        d[a] = (V.X(j, a) + V.U(j, a)) - (V.X(i, a) + V.U(i, a));
-        if (a < dim) d[a] = d[a] - L[a] * floor(d[a] / L[a] + 0.5);
-        dd += d[a] * d[a];
-      }
-      const double dist = sqrt(dd);
-      if (dist > ri + rj || dist == 0.0) continue;
-      double n[3], vn = 0;
-      for (int a = 0; a < 3; a++) {
-        n[a] = d[a] / dist;
-        vn += (V.U(j, a) - V.U(i, a)) * n[a];
-      }
-      if (!(vn < 0.0)) continue;
-      double W[3];
-      for (int a = 0; a < 3; a++) {
-        if (infA)
-          W[a] = V.U(i, a);
-        else if (infB)
-          W[a] = V.U(j, a);
-        else
-          W[a] = (mi * V.U(i, a) + mj * V.U(j, a)) / (mi + mj);
-      }
-      const int who[2] = {i, j};
-      for (int t2 = 0; t2 < 2; t2++) {
-        const int q = who[t2];
-        double wvv[3], wn = 0, v2 = 0;
-        for (int a = 0; a < 3; a++) {
-          wvv[a] = V.U(q, a) - W[a];
-          wn += wvv[a] * n[a];
-        }
-        for (int a = 0; a < 3; a++) {
-          const double u = W[a] + (wvv[a] - 2.0 * wn * n[a]);
-          V.U(q, a) = u;
-          v2 += u * u;
-        }
-        vseen = fmax(vseen, sqrt(v2));
-      }
+      collide_pair(V, pr.x, pr.y, L, dim, vseen);
     }
   }
   __syncthreads();
@@ -1178,15 +1240,7 @@ __global__ __launch_bounds__(NT) void k_particles(DevParticles P, int dim, Boxes
       b0[a] = one ? b0r[a] : P.b0[3 * p + a];
       og[a] = one ? ogr[a] : P.org[3 * p + a];
     }
-    if (G.walls && !isinf(m)) {
-      // contact with a wall after the pairs: the normal velocity reverses
-      // when the predicted surface reaches the BS layer while approaching
-      for (int a = 0; a < dim; a++) {
-        if (!(G.walls & (1 << a))) continue;
-        const double xp = x[a] + u[a];
-        if ((xp - r <= 1.0 && u[a] < 0.0) || (xp + r >= (double)(L[a] - 2) && u[a] > 0.0)) u[a] = -u[a];
-      }
-    }
+    bounce_walls(G, L, dim, m, r, x, u);
     int moved = 0;
     for (int a = 0; a < 3; a++) {
       P.u[3 * p + a] = u[a];
@@ -1212,6 +1266,40 @@ __global__ __launch_bounds__(NT) void k_particles(DevParticles P, int dim, Boxes
 // of the particle's stamps, and the list of particles close enough to collide
 // this step.  One workgroup per particle.
 // ---------------------------------------------------------------------------
+// A particle's rigid-body motion about its template's centre.
+struct RigidBody {
+  double phx, phy, phz, upx, upy, upz, wx, wy, wz;
+};
+__device__ __forceinline__ RigidBody rigid_body(const DevParticles& P, int p) {
+  return {P.phi[3 * p], P.phi[3 * p + 1], P.phi[3 * p + 2], P.u[3 * p],     P.u[3 * p + 1],
+          P.u[3 * p + 2], P.om[3 * p],    P.om[3 * p + 1],  P.om[3 * p + 2]};
+}
+// dp = rho_B (u_B' - u_B), dl = r x dp of one owned BS site with the
+// post-collision moments mv.
+__device__ __forceinline__ void add_exchange(const RigidBody& b, double rho0, int pk, const double4& mv,
+                                             double (&acc)[6]) {
+  const double rhoB = rho0 + mv.x;
+  const double ubx = mv.y / rhoB, uby = mv.z / rhoB, ubz = mv.w / rhoB;
+  const double rx = (double)off_x(pk) - b.phx, ry = (double)off_y(pk) - b.phy, rz = (double)off_z(pk) - b.phz;
+  const double vx = b.upx + (b.wy * rz - b.wz * ry);
+  const double vy = b.upy + (b.wz * rx - b.wx * rz);
+  const double vz = b.upz + (b.wx * ry - b.wy * rx);
+  const double dpx = rhoB * (vx - ubx), dpy = rhoB * (vy - uby), dpz = rhoB * (vz - ubz);
+  acc[0] += dpx;
+  acc[1] += dpy;
+  acc[2] += dpz;
+  acc[3] += ry * dpz - rz * dpy;
+  acc[4] += rz * dpx - rx * dpz;
+  acc[5] += rx * dpy - ry * dpx;
+}
+// Squared minimum-image distance between two centres of box G.
+__device__ __forceinline__ double image_dist2(const Geo& G, double dx, double dy, double dz) {
+  dx -= G.nx * floor(dx / G.nx + 0.5);
+  dy -= G.ny * floor(dy / G.ny + 0.5);
+  if (G.nz > 1) dz -= G.nz * floor(dz / G.nz + 0.5);
+  return dx * dx + dy * dy + dz * dz;
+}
+
 // GRID: site ownership is settled from kind grids after the particle update,
 // so the map and flags are not released here, and the particles that may
 // share a site with this one (both directions) are listed for it; otherwise
@@ -1229,9 +1317,7 @@ __global__ __launch_bounds__(NB) void k_reduce(int* __restrict__ own,
   const int lane = tid & 63, wv = tid >> 6;
   const Geo G = geo_of(BX, P, p);
   const int e0 = P.ent0[p], nbs = P.nbs[p], nis = P.nis[p], nin = P.nin[p];
-  const double phx = P.phi[3 * p], phy = P.phi[3 * p + 1], phz = P.phi[3 * p + 2];
-  const double upx = P.u[3 * p], upy = P.u[3 * p + 1], upz = P.u[3 * p + 2];
-  const double wx = P.om[3 * p], wy = P.om[3 * p + 1], wz = P.om[3 * p + 2];
+  const RigidBody rb = rigid_body(P, p);
   // the wrapped origin, loaded once (a load inside the entry loop would wait
   // for the map stores before it, which the compiler cannot prove distinct)
   const int ox0 = P.org[3 * p], oy0 = P.org[3 * p + 1], oz0 = P.org[3 * p + 2];
@@ -1242,14 +1328,6 @@ __global__ __launch_bounds__(NB) void k_reduce(int* __restrict__ own,
   const double xpx = P.x[3 * p], xpy = P.x[3 * p + 1], xpz = P.x[3 * p + 2];
   const double rp = P.rad[p];
   const int np = G.p1;
-  // squared minimum-image distance to (xj, yj, zj)
-  auto dist2 = [&](double xj, double yj, double zj) {
-    double dx = xj - xpx, dy = yj - xpy, dz = zj - xpz;
-    dx -= G.nx * floor(dx / G.nx + 0.5);
-    dy -= G.ny * floor(dy / G.ny + 0.5);
-    if (G.nz > 1) dz -= G.nz * floor(dz / G.nz + 0.5);
-    return dx * dx + dy * dy + dz * dz;
-  };
   // the scan runs over j > p, or over the whole box for the site-sharing list
   const int bq = BX.nbox == 1 ? 0 : P.box[p];
   const int jstart = GRID ? (bq == 0 ? 0 : BX.tab[bq - 1].p1) : p + 1;
@@ -1286,20 +1364,7 @@ __global__ __launch_bounds__(NB) void k_reduce(int* __restrict__ own,
       const int t = tb + j * NB + tid;
       const int pk = pkv[j];
       if (t >= ne || entry_kind(pk) != 1 || mv[j].x == kSlotUnowned) continue;  // owned BS sites only
-      // dp = rho_B (u_B' - u_B), dl = r x dp with the post-collision moments
-      const double rhoB = rho0 + mv[j].x;
-      const double ubx = mv[j].y / rhoB, uby = mv[j].z / rhoB, ubz = mv[j].w / rhoB;
-      const double rx = (double)off_x(pk) - phx, ry = (double)off_y(pk) - phy, rz = (double)off_z(pk) - phz;
-      const double vx = upx + (wy * rz - wz * ry);
-      const double vy = upy + (wz * rx - wx * rz);
-      const double vz = upz + (wx * ry - wy * rx);
-      const double dpx = rhoB * (vx - ubx), dpy = rhoB * (vy - uby), dpz = rhoB * (vz - ubz);
-      acc[0] += dpx;
-      acc[1] += dpy;
-      acc[2] += dpz;
-      acc[3] += ry * dpz - rz * dpy;
-      acc[4] += rz * dpx - rx * dpz;
-      acc[5] += rx * dpy - ry * dpx;
+      add_exchange(rb, rho0, pk, mv[j], acc);
     }
 #pragma unroll
     for (int j = 0; j < kEnt; j++) {
@@ -1350,7 +1415,7 @@ __global__ __launch_bounds__(NB) void k_reduce(int* __restrict__ own,
       zj = P.x[3 * jj + 2];
       rj = P.rad[jj];
     }
-    const double d2 = dist2(xj, yj, zj);
+    const double d2 = image_dist2(G, xj - xpx, yj - xpy, zj - xpz);
     const double lim = rp + rj + margin, lims = rp + rj + kShareMargin;
     const bool close = j < np && j > p && d2 <= lim * lim;
     const bool share = GRID && j < np && j != p && d2 <= lims * lims;
@@ -1729,46 +1794,36 @@ __device__ __forceinline__ int kind_at(const uint8_t* __restrict__ kg, int R, in
 
 constexpr int kGridBlock = kPrepareBlock;
 
+// A particle that may share a site: id, origin, kind-grid start and half-width.
+struct Neighbour {
+  int id, ox, oy, oz, kg0, kgR;
+};
+// The particle a prepare pass is for, at its new shift.
+struct Prepared {
+  int p, e0, ne;            // its entries (the BS and IS ones, and the interior ones where flags are written)
+  int ox, oy, oz;           // origin
+  int px, py, pz;           // origin before the last translation
+  int kg0, kgR;
+  RigidBody b;
+  bool jump, moved, flags;
+};
+
+// The runs of 64 entries that one wave of the pass takes: the entries come
+// kind by kind (BS, IS, interior), so they are dealt in runs (one wave each)
+// round-robin over all the waves of the particle's `split` workgroups, which
+// then share the IS substep's stores evenly: run c goes to workgroup c %
+// split, whose nwv waves take its runs in turn (this one: wave wv of part).
 template <int Q, typename T, bool NTS>
-__global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict__ flag,
-                                                             typename Store<T>::C* __restrict__ vel,
-                                                             double* __restrict__ slot,
-                                                             const typename Store<T>::C* __restrict__ drho,
-                                                             T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
-                                                             double rho0, int pending, int lay, int split,
-                                                             int flags_all) {
+__device__ __forceinline__ void prepare_entries(uint8_t* __restrict__ flag, typename Store<T>::C* __restrict__ vel,
+                                                double* __restrict__ slot,
+                                                const typename Store<T>::C* __restrict__ drho, T* __restrict__ S,
+                                                const uint8_t* __restrict__ kgrid, const DevEntries& E, const Geo& G,
+                                                const Prepared& a, const Neighbour* nb, int nn, double rho0,
+                                                int pending, int lay, int part, int split, int wv, int nwv, int lane) {
   using C = typename Store<T>::C;
   constexpr int DIM = Q == 9 ? 2 : 3;
-  __shared__ int s_nb[kNbrMax][6];  // neighbour id, origin, kind-grid start and half-width
-  const int p = blockIdx.x / split, part = blockIdx.x % split;
-  const int tid = threadIdx.x;
-  const Geo G = geo_of(BX, P, p);
-  const int ox0 = P.org[3 * p], oy0 = P.org[3 * p + 1], oz0 = P.org[3 * p + 2];
-  const double phx = P.phi[3 * p], phy = P.phi[3 * p + 1], phz = P.phi[3 * p + 2];
-  const double upx = P.u[3 * p], upy = P.u[3 * p + 1], upz = P.u[3 * p + 2];
-  const double wx = P.om[3 * p], wy = P.om[3 * p + 1], wz = P.om[3 * p + 2];
-  const C cupx = (C)upx, cupy = (C)upy, cupz = (C)upz, cwx = (C)wx, cwy = (C)wy, cwz = (C)wz;
-  const bool jump = P.jump[p] != 0;
-  const bool moved = P.moved[p] != 0;
-  const bool flags = flags_all != 0 || moved;
-  // interior entries come last and only write flags: skipped when the flags
-  // stand as they are
-  const int e0 = P.ent0[p], ne = P.nbs[p] + P.nis[p] + (flags ? P.nin[p] : 0);
-  const int nn = P.nbr_n[p];
-  const int Rp = P.kgR[p];
-  const uint8_t* kgp = P.kgrid + P.kg0[p];
-  if (nn > 0) {
-    for (int t = tid; t < nn; t += kGridBlock) {
-      const int q = P.nbr[(size_t)p * kNbrMax + t];
-      s_nb[t][0] = q;
-      s_nb[t][1] = P.org[3 * q];
-      s_nb[t][2] = P.org[3 * q + 1];
-      s_nb[t][3] = P.org[3 * q + 2];
-      s_nb[t][4] = P.kg0[q];
-      s_nb[t][5] = P.kgR[q];
-    }
-    __syncthreads();
-  }
+  const RigidBody& b = a.b;
+  const C cupx = (C)b.upx, cupy = (C)b.upy, cupz = (C)b.upz, cwx = (C)b.wx, cwy = (C)b.wy, cwz = (C)b.wz;
   // owner (lowest id claiming the site, INT_MAX for none) and its kind at
   // (x, y, z), given this particle's own kind there (0 if none); cov: some
   // ball covers the site
@@ -1778,42 +1833,36 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
     okind = 0;
     cov = kp != 0;
     if (!wall && (kp == 1 || kp == 2)) {
-      oid = p;
+      oid = a.p;
       okind = kp;
     }
     for (int t = 0; t < nn; t++) {
-      const int q = s_nb[t][0];
-      if (q > oid && cov) break;  // ascending ids: no lower claimer left
-      const int kq = kind_at<DIM>(P.kgrid + s_nb[t][4], s_nb[t][5], s_nb[t][1], s_nb[t][2], s_nb[t][3], G, x, y, z);
+      const Neighbour n = nb[t];
+      if (n.id > oid && cov) break;  // ascending ids: no lower claimer left
+      const int kq = kind_at<DIM>(kgrid + n.kg0, n.kgR, n.ox, n.oy, n.oz, G, x, y, z);
       cov = cov || kq != 0;
-      if (!wall && (kq == 1 || kq == 2) && q < oid) {
-        oid = q;
+      if (!wall && (kq == 1 || kq == 2) && n.id < oid) {
+        oid = n.id;
         okind = kq;
       }
     }
   };
-  // The entries come kind by kind (BS, IS, interior), so they are dealt in
-  // runs of 64 (one wave each) round-robin over the particle's split
-  // workgroups, which then share the IS substep's stores evenly: run c goes
-  // to workgroup c % split, whose waves take its runs in turn.
   constexpr int kEnt = 4;
-  const int wv = tid >> 6, lane = tid & 63;
-  constexpr int kWv = kGridBlock / 64;
-  auto run0 = [&](int m) { return (part + split * (kWv * m + wv)) * 64; };  // this wave's m-th run
-  for (int mb = 0; (part + split * kWv * mb) * 64 < ne; mb += kEnt) {
+  auto run0 = [&](int m) { return (part + split * (nwv * m + wv)) * 64; };  // this wave's m-th run
+  for (int mb = 0; (part + split * nwv * mb) * 64 < a.ne; mb += kEnt) {
     int pkv[kEnt];
     C dv[kEnt];
     int sv[kEnt];
 #pragma unroll
     for (int j = 0; j < kEnt; j++) {
-      if (run0(mb + j) >= ne) break;  // the same for the whole wave
-      pkv[j] = E.off[e0 + min(run0(mb + j) + lane, ne - 1)];
+      if (run0(mb + j) >= a.ne) break;  // the same for the whole wave
+      pkv[j] = E.off[a.e0 + min(run0(mb + j) + lane, a.ne - 1)];
     }
 #pragma unroll
     for (int j = 0; j < kEnt; j++) {
-      if (run0(mb + j) >= ne) break;
+      if (run0(mb + j) >= a.ne) break;
       const int pk = pkv[j];
-      sv[j] = site_of(G, wrap1(ox0 + off_x(pk), G.nx), wrap1(oy0 + off_y(pk), G.ny), wrap1(oz0 + off_z(pk), G.nz));
+      sv[j] = site_of(G, wrap1(a.ox + off_x(pk), G.nx), wrap1(a.oy + off_y(pk), G.ny), wrap1(a.oz + off_z(pk), G.nz));
       // used only at an IS site the substep claims: runs of BS entries (the
       // first of a particle's entries) load nothing
       dv[j] = entry_kind(pk) == 2 ? drho[sv[j]] : C(0);
@@ -1821,45 +1870,44 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
 #pragma unroll 1
     for (int j = 0; j < kEnt; j++) {
       const int t = run0(mb + j) + lane;
-      if (t >= ne) continue;
-      const int e = e0 + t;
+      if (t >= a.ne) continue;
+      const int e = a.e0 + t;
       const int pk = pkv[j];
       const int ox = off_x(pk), oy = off_y(pk), oz = off_z(pk), kp = entry_kind(pk);
       const int s = sv[j];
-      const int sxx = wrap1(ox0 + ox, G.nx), syy = wrap1(oy0 + oy, G.ny), szz = wrap1(oz0 + oz, G.nz);
+      const int sxx = wrap1(a.ox + ox, G.nx), syy = wrap1(a.oy + oy, G.ny), szz = wrap1(a.oz + oz, G.nz);
       int oid, okind;
       bool cov;
       settle(sxx, syy, szz, kp, oid, okind, cov);
-      const bool mine = oid == p;
+      const bool mine = oid == a.p;
       if (pending && mine && kp == 2) {
         double dr;
-        if (jump) {
+        if (a.jump) {
           dr = 0;
 #pragma unroll
           for (int k = 0; k < Q; k++) dr += (double)pop_ld<Q, T>(S + coll_index<Q>(lay, k, G, sxx, syy, szz), k);
         } else {
           dr = (double)dv[j];
         }
-        impose_is<Q, T, NTS>(S, lay, G, sxx, syy, szz, dr, (C)((double)ox - phx), (C)((double)oy - phy),
-                             (C)((double)oz - phz), cupx, cupy, cupz, cwx, cwy, cwz, rho0);
+        impose_is<Q, T, NTS>(S, lay, G, sxx, syy, szz, dr, (C)((double)ox - b.phx), (C)((double)oy - b.phy),
+                             (C)((double)oz - b.phz), cupx, cupy, cupz, cwx, cwy, cwz, rho0);
       }
-      if (flags) flag[s] = okind == 1 ? kSiteBS : kSiteBall;
+      if (a.flags) flag[s] = okind == 1 ? kSiteBS : kSiteBall;
       if (mine && kp == 1) {
-        const double rx = (double)ox - phx, ry = (double)oy - phy, rz = (double)oz - phz;
-        vel[4 * (size_t)s] = (C)(upx + (wy * rz - wz * ry));
-        vel[4 * (size_t)s + 1] = (C)(upy + (wz * rx - wx * rz));
-        vel[4 * (size_t)s + 2] = (C)(upz + (wx * ry - wy * rx));
+        const double rx = (double)ox - b.phx, ry = (double)oy - b.phy, rz = (double)oz - b.phz;
+        vel[4 * (size_t)s] = (C)(b.upx + (b.wy * rz - b.wz * ry));
+        vel[4 * (size_t)s + 1] = (C)(b.upy + (b.wz * rx - b.wx * rz));
+        vel[4 * (size_t)s + 2] = (C)(b.upz + (b.wx * ry - b.wy * rx));
         vel[4 * (size_t)s + 3] = idx_as<C>(e);
       } else if (kp == 1) {
         slot[4 * (size_t)e] = kSlotUnowned;  // a BS entry whose site another particle or a wall holds
       }
-      if (moved) {
+      if (a.moved) {
         // the site this entry held before the translation: cleared unless a
         // ball still covers it (this particle's new ball covers it through
         // one of its own entries, which writes the flag there)
-        const int xo = wrap1(P.orgp[3 * p] + ox, G.nx), yo = wrap1(P.orgp[3 * p + 1] + oy, G.ny),
-                  zo = wrap1(P.orgp[3 * p + 2] + oz, G.nz);
-        if (kind_at<DIM>(kgp, Rp, ox0, oy0, oz0, G, xo, yo, zo) == 0) {
+        const int xo = wrap1(a.px + ox, G.nx), yo = wrap1(a.py + oy, G.ny), zo = wrap1(a.pz + oz, G.nz);
+        if (kind_at<DIM>(kgrid + a.kg0, a.kgR, a.ox, a.oy, a.oz, G, xo, yo, zo) == 0) {
           int qo, qk;
           bool qc;
           settle(xo, yo, zo, 0, qo, qk, qc);
@@ -1867,6 +1915,441 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
         }
       }
     }
+  }
+}
+
+template <int Q, typename T, bool NTS>
+__global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict__ flag,
+                                                             typename Store<T>::C* __restrict__ vel,
+                                                             double* __restrict__ slot,
+                                                             const typename Store<T>::C* __restrict__ drho,
+                                                             T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
+                                                             double rho0, int pending, int lay, int split,
+                                                             int flags_all) {
+  __shared__ Neighbour s_nb[kNbrMax];
+  const int p = blockIdx.x / split, part = blockIdx.x % split;
+  const int tid = threadIdx.x;
+  const Geo G = geo_of(BX, P, p);
+  Prepared a;
+  a.p = p;
+  a.ox = P.org[3 * p];
+  a.oy = P.org[3 * p + 1];
+  a.oz = P.org[3 * p + 2];
+  a.b = rigid_body(P, p);
+  a.jump = P.jump[p] != 0;
+  a.moved = P.moved[p] != 0;
+  a.flags = flags_all != 0 || a.moved;
+  // interior entries come last and only write flags: skipped when the flags
+  // stand as they are
+  a.e0 = P.ent0[p];
+  a.ne = P.nbs[p] + P.nis[p] + (a.flags ? P.nin[p] : 0);
+  const int nn = P.nbr_n[p];
+  a.kgR = P.kgR[p];
+  a.kg0 = P.kg0[p];
+  a.px = P.orgp[3 * p];
+  a.py = P.orgp[3 * p + 1];
+  a.pz = P.orgp[3 * p + 2];
+  if (nn > 0) {
+    for (int t = tid; t < nn; t += kGridBlock) {
+      const int q = P.nbr[(size_t)p * kNbrMax + t];
+      s_nb[t] = {q, P.org[3 * q], P.org[3 * q + 1], P.org[3 * q + 2], P.kg0[q], P.kgR[q]};
+    }
+    __syncthreads();
+  }
+  prepare_entries<Q, T, NTS>(flag, vel, slot, drho, S, P.kgrid, E, G, a, s_nb, nn, rho0, pending, lay, part, split,
+                             tid >> 6, kGridBlock / 64, tid & 63);
+}
+
+// ---------------------------------------------------------------------------
+// Boxes of at most kFewParticles particles: the particles' whole part of a
+// step -- the sums, the closure, the update and the prepare pass -- in one
+// workgroup per box, in one launch instead of three (four).  What such a box
+// needs of each is a chain of a few dependent loads, and a launch boundary
+// costs 1.9 us; within a workgroup the stages hand their results over in LDS.
+// Teams of 256 threads take the particles in turn for the sums (as k_reduce
+// does, in the same order); all of them share the prepare pass; one more wave
+// finds the close pairs and runs the closure network meanwhile.  The largest
+// balls' scattered IS stores want more than one CU: those keep the separate
+// kernels (fuse_ok).  One disk in 64^2 FP64: step 14.6 -> 9.9 us; 16 boxes of
+// two disks with the closure 36.4 -> 16.1 us; one sphere in 100 x 100 x 160
+// FP64 101 -> 95.5 us.
+// ---------------------------------------------------------------------------
+constexpr int kFewParticles = 4;
+constexpr int kFewPairs = kFewParticles * (kFewParticles - 1) / 2;
+constexpr int kFewTeams = 3;
+constexpr int kTeam = kBoundaryBlock;
+
+// The closure in k_box (CLO: it is on).
+struct ClosureArgs {
+  const mlp::f4* packed;
+  double h_max, mu, tau;
+};
+
+// The network for up to 16 pairs of one wave.  Its weight operands lie packed
+// in the workspace, one record per lane as the products take them (packed once
+// by lbm_set_closure): 21 wide loads that run while the pairs are found.  Read
+// from the flat parameters they took 130 loads and 8 us.
+struct ClosureWeights {
+  mlp::h4 w1[4], w2[4][4], w3[4];
+  mlp::f4 b1[4], b2[4], b3;
+};
+constexpr int kClosureParts = sizeof(ClosureWeights) / 16;  // 16-byte parts of a record
+static_assert(sizeof(ClosureWeights) % 16 == 0, "whole parts");
+// Part k of lane l's record is element [k][l] of the packed operands.
+__global__ __launch_bounds__(64) void k_pack_closure(const float* __restrict__ params, mlp::f4* __restrict__ packed) {
+  __shared__ mlp::Weights w;
+  const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+  mlp::load_weights(w, params, lane, 64);
+  __syncthreads();
+  ClosureWeights c;
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    c.w1[mt] = mlp::ld4(&w.w1t[16 * mt + r][4 * g]);
+    c.w3[mt] = mlp::ld4(&w.w3t[r][16 * mt + 4 * g]);
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) c.w2[mt][kt] = mlp::ld4(&w.w2t[16 * mt + r][16 * kt + 4 * g]);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      c.b1[mt][i] = w.b1[16 * mt + 4 * g + i];
+      c.b2[mt][i] = w.b2[16 * mt + 4 * g + i];
+    }
+  }
+  c.b3 = mlp::f4{w.b3[0], w.b3[1], 0.f, 0.f};
+  mlp::f4 part[kClosureParts];
+  __builtin_memcpy(part, &c, sizeof(c));
+#pragma unroll
+  for (int k = 0; k < kClosureParts; k++) packed[k * 64 + lane] = part[k];
+}
+__device__ __forceinline__ void closure_load(const mlp::f4* __restrict__ packed, int lane, ClosureWeights& c) {
+  mlp::f4 part[kClosureParts];
+#pragma unroll
+  for (int k = 0; k < kClosureParts; k++) part[k] = packed[k * 64 + lane];
+  __builtin_memcpy(&c, part, sizeof(c));
+}
+__device__ __forceinline__ void closure_network(const ClosureWeights& c, mlp::h4 xb, float& y0, float& y1) {
+  const mlp::f4 zero = {0.f, 0.f, 0.f, 0.f};
+  mlp::h4 h1[4], h2[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    const mlp::f4 acc = mlp::mma(c.w1[mt], xb, zero);
+#pragma unroll
+    for (int i = 0; i < 4; i++) h1[mt][i] = (_Float16)mlp::tanh_fast(acc[i] + c.b1[mt][i]);
+  }
+#pragma unroll
+  for (int mt = 0; mt < 4; mt++) {
+    mlp::f4 acc = zero;
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++) acc = mlp::mma(c.w2[mt][kt], h1[kt], acc);
+#pragma unroll
+    for (int i = 0; i < 4; i++) h2[mt][i] = (_Float16)mlp::tanh_fast(acc[i] + c.b2[mt][i]);
+  }
+  mlp::f4 y = zero;
+#pragma unroll
+  for (int kt = 0; kt < 4; kt++) y = mlp::mma(c.w3[kt], h2[kt], y);
+  y0 = y[0] + c.b3[0];
+  y1 = y[1] + c.b3[1];
+}
+
+// What the update needs of one particle besides the sums.
+struct FewInputs {
+  double m, I, rad, u[3], om[3], x[3], x0[3], fe[3], ph[3];
+  int k0[3], b0[3], og[3], ent0, nbs, nis, nin, kg0, kgR;
+};
+
+// What it leaves besides what the prepare pass needs.
+struct FewOutputs {
+  double F[3], T[3], x[3];
+  int k[3];
+};
+
+template <int Q, typename T, bool NTS, bool CLO>
+__global__ __launch_bounds__(kTeam * kFewTeams + 64) void k_box(
+    uint8_t* __restrict__ flag, typename Store<T>::C* __restrict__ vel, double* __restrict__ slot,
+    const typename Store<T>::C* __restrict__ drho, T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
+    double rho0, double margin, ClosureArgs clo, int lay, int* status) {
+  constexpr int DIM = Q == 9 ? 2 : 3;
+  __shared__ double s_part[kFewParticles][kTeam / 64][6];
+  __shared__ double s_x[3 * kFewParticles], s_u[3 * kFewParticles], s_m[kFewParticles], s_r[kFewParticles];
+  __shared__ double s_fc[kFewParticles][3];
+  __shared__ int s_cand[kFewPairs], s_share[kFewPairs], s_cnt[kFewParticles];
+  __shared__ FewInputs s_in[kFewParticles];
+  __shared__ Prepared s_a[kFewParticles];
+  __shared__ FewOutputs s_out[kFewParticles];
+  __shared__ Neighbour s_nb[kFewParticles][kFewParticles - 1];
+  const int box = blockIdx.x;
+  const Geo G = BX.nbox == 1 ? BX.g0 : BX.tab[box];
+  const int p0 = box == 0 ? 0 : BX.tab[box - 1].p1, n = G.p1 - p0;
+  if (n <= 0) return;  // an empty box
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int teams = ((int)blockDim.x - 64) / kTeam, team = tid / kTeam;
+  const bool aux = team == teams;  // the last wave
+  const int L[3] = {G.nx, G.ny, G.nz};
+
+  if (!aux) {
+    // eq. 6-9: the sums of k_reduce
+    const int tt = tid - team * kTeam;
+    for (int q = team; q < n; q += teams) {
+      const int p = p0 + q;
+      const RigidBody rb = rigid_body(P, p);
+      const int e0 = P.ent0[p], ne = P.nbs[p];
+      double acc[6] = {0, 0, 0, 0, 0, 0};
+      constexpr int kEnt = 4;
+      for (int tb = 0; tb < ne; tb += kTeam * kEnt) {
+        int pkv[kEnt];
+        double4 mv[kEnt];
+#pragma unroll
+        for (int j = 0; j < kEnt; j++) {
+          if (tb + j * kTeam >= ne) break;
+          const int e = e0 + min(tb + j * kTeam + tt, ne - 1);
+          pkv[j] = E.off[e];
+          mv[j] = *(const double4*)(slot + 4 * (size_t)e);
+        }
+#pragma unroll
+        for (int j = 0; j < kEnt; j++) {
+          if (tb + j * kTeam >= ne) break;
+          if (tb + j * kTeam + tt >= ne || entry_kind(pkv[j]) != 1 || mv[j].x == kSlotUnowned) continue;
+          add_exchange(rb, rho0, pkv[j], mv[j], acc);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 6; c++) {
+        const double v = wave_sum(acc[c]);
+        if (lane == 0) s_part[q][tt >> 6][c] = v;
+      }
+    }
+  } else {
+    [[maybe_unused]] ClosureWeights cw;
+    if constexpr (CLO) closure_load(clo.packed, lane, cw);
+    // the update's inputs, staged (in registers they would crowd the sums)
+    if (lane < n) {
+      const int p = p0 + lane;
+      FewInputs v;
+      v.m = P.m[p];
+      v.I = P.I[p];
+      v.rad = P.rad[p];
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        v.u[a] = P.u[3 * p + a];
+        v.om[a] = P.om[3 * p + a];
+        v.x[a] = P.x[3 * p + a];
+        v.x0[a] = P.x0[3 * p + a];
+        v.fe[a] = P.fext[3 * p + a];
+        v.ph[a] = P.phi[3 * p + a];
+        v.k0[a] = P.k[3 * p + a];
+        v.b0[a] = P.b0[3 * p + a];
+        v.og[a] = P.org[3 * p + a];
+      }
+      v.ent0 = P.ent0[p];
+      v.nbs = P.nbs[p];
+      v.nis = P.nis[p];
+      v.nin = P.nin[p];
+      v.kg0 = P.kg0[p];
+      v.kgR = P.kgR[p];
+      s_in[lane] = v;
+    }
+    // pairs i < j in lexicographic order, one lane each: close enough to
+    // collide, or to share a site after the translation
+    const int np = n * (n - 1) / 2;
+    int i = 0, j = 0;
+    bool close = false;
+    double dx = 0, dy = 0, dz = 0;
+    if (lane < np) {
+      int k = lane;
+      while (k >= n - 1 - i) k -= n - 1 - i++;
+      j = i + 1 + k;
+      const int pi = p0 + i, pj = p0 + j;
+      dx = P.x[3 * pj] - P.x[3 * pi];
+      dy = P.x[3 * pj + 1] - P.x[3 * pi + 1];
+      dz = P.x[3 * pj + 2] - P.x[3 * pi + 2];
+      const double d2 = image_dist2(G, dx, dy, dz), rr = P.rad[pi] + P.rad[pj];
+      const double lim = rr + margin, lims = rr + kShareMargin;
+      close = d2 <= lim * lim;
+      s_cand[lane] = close;
+      s_share[lane] = d2 <= lims * lims;
+    }
+    if (lane < 3 * kFewParticles) s_fc[lane / 3][lane % 3] = 0.0;
+    if constexpr (CLO) {
+      dx -= G.nx * floor(dx / G.nx + 0.5);
+      dy -= G.ny * floor(dy / G.ny + 0.5);
+      const double dist = sqrt(dx * dx + dy * dy);
+      const bool acts = close && dist - P.rad[p0 + i] - P.rad[p0 + j] < clo.h_max;
+      if (__ballot(acts)) {
+        // inputs of pair `lane`, its features 4g .. 4g+3 to lane 16 g + pair
+        float in[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (acts)
+          mlp::closure_inputs(P.x[3 * (p0 + i)], P.x[3 * (p0 + i) + 1], P.rad[p0 + i], P.rad[p0 + j], dx, dy, clo.tau,
+                              in);
+        mlp::h4 xb;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          const float lo = __shfl(in[k], lane & 15), hi = __shfl(in[4 + k], lane & 15);
+          xb[k] = (_Float16)(lane < 16 ? lo : lane < 32 ? hi : 0.0f);
+        }
+        float y0, y1;
+        closure_network(cw, xb, y0, y1);
+        double fx = 0, fy = 0;
+        if (acts) {
+          const double nx = dx / dist, ny = dy / dist;
+          const double U = (P.u[3 * (p0 + i)] - P.u[3 * (p0 + j)]) * nx +
+                           (P.u[3 * (p0 + i) + 1] - P.u[3 * (p0 + j) + 1]) * ny;
+          const double an = (double)y0, at = (double)y1;
+          fx = clo.mu * U * (an * nx + at * -ny);
+          fy = clo.mu * U * (an * ny + at * nx);
+        }
+        // every particle's sum over its pairs in list order (+ as i, - as j)
+        double sx = 0, sy = 0;
+        for (int k = 0; k < np; k++) {
+          const int ki = __shfl(i, k), kj = __shfl(j, k);
+          const bool on = __shfl((int)acts, k) != 0;
+          const double kx = __shfl(fx, k), ky = __shfl(fy, k);
+          if (!on) continue;
+          if (lane == ki) {
+            sx += kx;
+            sy += ky;
+          } else if (lane == kj) {
+            sx -= kx;
+            sy -= ky;
+          }
+        }
+        if (lane < n) {
+          s_fc[lane][0] = sx;
+          s_fc[lane][1] = sy;
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  if (wv == 0) {
+    // eq. 10-11, 16-19, 13: the update of k_particles
+    const bool mover = lane < n;
+    const FewInputs& in = s_in[mover ? lane : 0];
+    double dp[3] = {0, 0, 0}, dl[3] = {0, 0, 0}, fc[3] = {0, 0, 0}, v2 = 0;
+    double u[3], om[3], x[3];
+    const double m = in.m, rad = in.rad;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      u[a] = in.u[a];
+      om[a] = in.om[a];
+      x[a] = in.x[a];
+    }
+    if (mover) {
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+#pragma unroll
+        for (int w = 0; w < kTeam / 64; w++) {
+          dp[a] += s_part[lane][w][a];
+          dl[a] += s_part[lane][w][3 + a];
+        }
+        fc[a] = s_fc[lane][a];
+      }
+      v2 = accelerate(m, in.I, dp, dl, fc, in.fe, u, om);
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        s_x[3 * lane + a] = x[a];
+        s_u[3 * lane + a] = u[a];
+      }
+      s_m[lane] = m;
+      s_r[lane] = rad;
+    }
+    double vmax = sqrt(v2);
+    for (int o = kFewParticles / 2; o > 0; o >>= 1) vmax = fmax(vmax, __shfl_xor(vmax, o));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) {
+      const PartView V{s_x, s_u, s_m, s_r, 1, 3, 0};
+      double vseen = vmax;
+      int k = 0;
+      for (int i = 0; i < n; i++)
+        for (int j = i + 1; j < n; j++, k++)
+          if (s_cand[k]) collide_pair(V, i, j, L, DIM, vseen);
+      if (2.0 * vseen >= kMargin) atomicOr(status, kStatusCollision);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (mover) {
+#pragma unroll
+      for (int a = 0; a < 3; a++) u[a] = s_u[3 * lane + a];
+      bounce_walls(G, L, DIM, m, rad, x, u);
+      int moved = 0, on[3] = {in.og[0], in.og[1], in.og[2]};
+      FewOutputs out;
+#pragma unroll
+      for (int a = 0; a < 3; a++) {
+        out.F[a] = -dp[a] + fc[a];
+        out.T[a] = -dl[a];
+        if (a < DIM) {
+          out.x[a] = x[a] + u[a];
+          out.k[a] = (int)floor(out.x[a] - in.x0[a] + 0.5);
+          moved += out.k[a] != in.k0[a];
+          on[a] = wrap(in.b0[a] + out.k[a], L[a]);
+        }
+      }
+      Prepared pr;
+      pr.p = p0 + lane;
+      pr.e0 = in.ent0;
+      pr.ne = in.nbs + in.nis + (moved ? in.nin : 0);
+      pr.ox = on[0];
+      pr.oy = on[1];
+      pr.oz = on[2];
+      pr.px = in.og[0];
+      pr.py = in.og[1];
+      pr.pz = in.og[2];
+      pr.kg0 = in.kg0;
+      pr.kgR = in.kgR;
+      pr.b = {in.ph[0], in.ph[1], in.ph[2], u[0], u[1], u[2], om[0], om[1], om[2]};
+      pr.jump = moved == 3;
+      pr.moved = pr.flags = moved != 0;
+      s_a[lane] = pr;
+      s_out[lane] = out;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    // the particles that may share a site with each, in ascending order
+    if (mover) {
+      int c = 0;
+      for (int q = 0; q < n; q++) {
+        if (q == lane) continue;
+        const int i = min(q, lane), j = max(q, lane);
+        if (!s_share[i * n - i * (i + 1) / 2 + j - i - 1]) continue;
+        s_nb[lane][c++] = {p0 + q, s_a[q].ox, s_a[q].oy, s_a[q].oz, s_a[q].kg0, s_a[q].kgR};
+      }
+      s_cnt[lane] = c;
+    }
+  }
+  __syncthreads();
+  // the new state to memory, after the last barrier: a barrier waits for the
+  // stores before it
+  if (aux && lane < n) {
+    const int p = p0 + lane;
+    const Prepared& pr = s_a[lane];
+    const FewOutputs& out = s_out[lane];
+    const double un[3] = {pr.b.upx, pr.b.upy, pr.b.upz}, wn[3] = {pr.b.wx, pr.b.wy, pr.b.wz};
+    const int on[3] = {pr.ox, pr.oy, pr.oz}, og[3] = {pr.px, pr.py, pr.pz};
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      P.F[3 * p + a] = out.F[a];
+      P.T[3 * p + a] = out.T[a];
+      P.u[3 * p + a] = un[a];
+      P.om[3 * p + a] = wn[a];
+      P.orgp[3 * p + a] = og[a];
+      if (a < DIM) {
+        P.x[3 * p + a] = out.x[a];
+        P.k[3 * p + a] = out.k[a];
+        P.org[3 * p + a] = on[a];
+      }
+    }
+    P.jump[p] = pr.jump;
+    P.moved[p] = pr.moved;
+  }
+  // the prepare pass: every whole team's waves on each particle in turn, or
+  // shared out when there are more particles than one
+  const int waves = (int)blockDim.x / 64, per = waves / n;
+  for (int q = 0; q < n; q++) {
+    if (wv < q * per || wv >= (q + 1) * per) continue;
+    prepare_entries<Q, T, NTS>(flag, vel, slot, drho, S, P.kgrid, E, G, s_a[q], s_nb[q], s_cnt[q], rho0, 1, lay, 0, 1,
+                               wv - q * per, per, lane);
   }
 }
 
@@ -1985,7 +2468,7 @@ struct Layout {
       pairs;
   size_t orgp, moved, kg0, kgR, nbr_n, nbr, kgrid;
   size_t off, pid, slot, vel;
-  size_t boxes, fbt, tiles, fc, clo;
+  size_t boxes, fbt, tiles, fc, clo, clo_packed;
   int64_t max_ent, max_tiles;
   size_t total;
 };
@@ -2094,6 +2577,7 @@ Layout make_layout(const lbm_params& p, const BoxSet& bs) {
   L.tiles = take(3 * sizeof(int4) * bs.max_tiles);
   L.fc = take(sizeof(double) * 3 * np);
   L.clo = take(sizeof(float) * mlp::kParams);
+  L.clo_packed = take(sizeof(ClosureWeights) * 64);
   L.total = cur;
   return L;
 }
@@ -2360,6 +2844,7 @@ struct lbm_ctx {
   int closure;              // near-contact closure network on
   double clo_h;             // gap below which it acts
   float* d_clo;             // its parameters
+  mlp::f4* d_clo_packed;    // and the same as operands (k_pack_closure)
   hipStream_t stream;
   char* ws;
   Layout L;
@@ -2381,6 +2866,8 @@ struct lbm_ctx {
                       // owner map rebuilt every step and one thread per entry)
   bool small_grid;    // no ball is so large that a box of many gives the grids up
   size_t kg_used;     // bytes of kind grids in use
+  int box_most;       // most particles of one box
+  int64_t box_entries;  // most BS and IS entries of one box's particles
   int prep_split;     // most workgroups per particle of the per-particle prepare
   bool small_ball;    // the largest ball holds at most kSmallBall entries
   bool prof;
@@ -2393,6 +2880,21 @@ struct lbm_ctx {
 // Layout of the state between steps: the AA pattern alternates its two
 // halves with the step parity (cur), kept like the buffer index of two arrays.
 int state_layout(const lbm_ctx* c) { return c->prm.aa ? (c->cur == 0 ? kLayAAStream : kLayAASwap) : kLayAB; }
+
+// Whether one workgroup per box does the particles' part of a step (k_box): no
+// box holds more than kFewParticles, and its particles' BS and IS entries times
+// their number stay below what one CU does in the time of two launch
+// boundaries.  Step of one FP32 box, fused against separate launches: 300^2
+// with two disks of radius 48 (3,008) 14.4 / 16.0 us, with four of radius 24
+// (5,888) 15.9 / 15.7; 100 x 100 x 60 with one sphere of radius 7.5 (1,299)
+// 30.2 / 34.1 us, with four of radius 3 (1,808) 30.4 / 32.9, with one of 12
+// (3,793) 39.4 / 36.7 (each IS site has 19 scattered stores there).  The list
+// of close pairs has no global bound here, so with the closure on there must
+// be no more pairs than the separate kernel's list holds.
+bool fuse_ok(const lbm_ctx* c) {
+  return c->grids && c->box_most <= kFewParticles && c->box_entries * c->box_most <= (c->dim == 2 ? 3200 : 2000) &&
+         (!c->closure || (int64_t)c->nbox * kFewPairs <= kClosurePairs);
+}
 
 // Launch shapes: widths 64..512 are the tile kernel, 0 the one-box kernel.
 bool tile_width(int w) { return w == 64 || w == 128 || w == 256 || w == 512; }
@@ -2446,17 +2948,38 @@ int launch_prepare_as(lbm_ctx* c, int pending, int flags_all) {
   return LBM_OK;
 }
 
+// Streaming IS stores for the AA pattern (the in-place sweep pays most for
+// partly written lines) and for two arrays small enough to stay in the
+// last-level cache (D2Q9 1024^2, 75 MB: step 33.2 -> 32.0 us); larger
+// two-array states keep plain stores (256^3 FP32: 0.456 against 0.464 ms).
+bool streaming_is(const lbm_ctx* c) {
+  const size_t both = 2 * (size_t)c->q * c->PS * store_size(c->prm.storage);
+  return state_layout(c) != kLayAB || both <= kCacheResidentBytes;
+}
+
 template <int Q, typename T>
 int launch_prepare(lbm_ctx* c, int pending, int flags_all) {
   if (c->nent == 0) return LBM_OK;
-  // Streaming IS stores for the AA pattern (the in-place sweep pays most for
-  // partly written lines) and for two arrays small enough to stay in the
-  // last-level cache (D2Q9 1024^2, 75 MB: step 33.2 -> 32.0 us); larger
-  // two-array states keep plain stores (256^3 FP32: 0.456 against 0.464 ms).
-  const size_t both = 2 * (size_t)c->q * c->PS * store_size(c->prm.storage);
-  const bool nts = state_layout(c) != kLayAB || both <= kCacheResidentBytes;
-  return nts ? launch_prepare_as<Q, T, true>(c, pending, flags_all)
-             : launch_prepare_as<Q, T, false>(c, pending, flags_all);
+  return streaming_is(c) ? launch_prepare_as<Q, T, true>(c, pending, flags_all)
+                         : launch_prepare_as<Q, T, false>(c, pending, flags_all);
+}
+
+// The particles' part of a step of boxes with few particles (fuse_ok); c->cur
+// names the state the sweep just wrote.
+template <int Q, typename T>
+int launch_box(lbm_ctx* c) {
+  using C = typename Store<T>::C;
+  const double margin = c->closure ? std::max(kMargin, c->clo_h) : kMargin;
+  const ClosureArgs clo = {c->d_clo_packed, c->clo_h, c->prm.rho0 * (c->prm.tau - 0.5) / 3.0,
+                           c->prm.tau};
+  const int block = kTeam * std::min(kFewTeams, std::max(c->box_most, c->prep_split)) + 64;
+  auto* kernel = streaming_is(c) ? k_box<Q, T, true, false> : k_box<Q, T, false, false>;
+  if constexpr (Q == 9)
+    if (c->closure) kernel = streaming_is(c) ? k_box<Q, T, true, true> : k_box<Q, T, false, true>;
+  kernel<<<c->nbox, block, 0, c->stream>>>(c->flag, (C*)c->vel, c->slot, (const C*)c->drho, (T*)c->f[c->cur], c->P, c->E,
+                                           boxes_arg(c), c->prm.rho0, margin, clo, state_layout(c), c->status);
+  HIP_TRY(hipGetLastError());
+  return LBM_OK;
 }
 
 // Tile list {box, y, z, x0} of width w, box by box, rows in z, y order.
@@ -2616,6 +3139,10 @@ int launch_step(lbm_ctx* c) {
   if (c->prof) {
     HIP_TRY(hipEventRecord(c->ev[c->ev_used + 1], c->stream));
     c->ev_used += 2;
+  }
+  if (c->np > 0 && fuse_ok(c)) {
+    c->cur = 1 - c->cur;
+    return launch_box<Q, T>(c);
   }
   if (c->np > 0) {
     const Boxes bx = boxes_arg(c);
@@ -2973,6 +3500,7 @@ static int create_impl(const lbm_params* prm, int nbox, const int32_t* dims, voi
                       (int*)(w + L.nbr_n),   (int*)(w + L.nbr),
                       (uint8_t*)(w + L.kgrid)};
   c->d_clo = (float*)(w + L.clo);
+  c->d_clo_packed = (mlp::f4*)(w + L.clo_packed);
   c->closure = 0;
   c->clo_h = 0.0;
   c->E = DevEntries{(int*)(w + L.off), (int*)(w + L.pid)};
@@ -2988,6 +3516,8 @@ static int create_impl(const lbm_params* prm, int nbox, const int32_t* dims, voi
     c->grids = true;
     c->small_grid = small_grids(c->dim, prm->max_radius);
     c->kg_used = 0;
+    c->box_most = 0;
+    c->box_entries = 0;
     // about one workgroup per kPrepareBlock entries of the largest ball (its
     // volume), so that a particle's scattered IS stores spread over CUs; a
     // large ball's entries are mostly interior, which most steps skip
@@ -3278,6 +3808,10 @@ static int add_impl(lbm_ctx* c, int32_t bx, int32_t n, const double* x, const do
   c->h_off.insert(c->h_off.end(), hoff.begin(), hoff.end());
   c->h_pid.insert(c->h_pid.end(), hpid.begin(), hpid.end());
   c->h_box.insert(c->h_box.end(), (size_t)n, bx);
+  int64_t entries = 0;
+  for (int p = pbox0; p < c->np; p++) entries += c->h_nbs[p] + c->h_nis[p];
+  c->box_most = std::max(c->box_most, c->np - pbox0);
+  c->box_entries = std::max(c->box_entries, entries);
   drop_graph(c);
   if (first_id) *first_id = p0;
   return LBM_OK;
@@ -3597,8 +4131,10 @@ int lbm_set_closure(lbm_ctx* c, const float* d_params, double h_max) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->closure = d_params != nullptr && h_max > 0;
   c->clo_h = h_max;
-  if (d_params)
+  if (d_params) {
     HIP_TRY(hipMemcpyAsync(c->d_clo, d_params, sizeof(float) * mlp::kParams, hipMemcpyDeviceToDevice, c->stream));
+    k_pack_closure<<<1, 64, 0, c->stream>>>(c->d_clo, c->d_clo_packed);
+  }
   if (!c->closure && c->np > 0)
     k_fill<double><<<blocks_for(3 * (int64_t)c->np), 256, 0, c->stream>>>(c->P.fc, 3 * (int64_t)c->np, 0.0);
   HIP_TRY(hipGetLastError());
