@@ -2398,7 +2398,10 @@ __global__ void k_owners(const int* __restrict__ own, const int* __restrict__ pi
 // pinned host memory: kHostHead bytes, then the arrays.  One launch and one
 // wait, where five copies to pageable memory and the status word's took 90 us.
 constexpr size_t kHostHead = 64;
-constexpr size_t kFieldBlock = (size_t)4 << 20;  // pinned block of a field read-out
+// Pinned block of a field read-out (there are two): 256^3 in blocks of 4, 8 and
+// 16 MB 21.6, 17.3 and 14.9 ms; pinning two of 16 MB costs the first read-out
+// what later ones gain.
+constexpr size_t kFieldBlock = (size_t)8 << 20;
 constexpr int kHostParticles = 16384;  // most particles read out that way (2 MB)
 __global__ void k_read_particles(DevParticles P, const int* __restrict__ status, int n3, char* __restrict__ host) {
   const int i = blockIdx.x * 256 + threadIdx.x;

@@ -1,5 +1,5 @@
 """Read-outs through pinned blocks: fields in one and in several chunks (the
-chunk is 116,508 sites) that end inside boxes of an ensemble, each of the
+chunk is 233,016 sites) that end inside boxes of an ensemble, each of the
 three arrays alone and in pairs, both population layouts, particle read-outs
 with the context's pinned block and without (above 16,384 particles), and two
 contexts read from two threads at once.  References: the moments of the
@@ -55,7 +55,7 @@ def _check(sim):
 
 
 @pytest.mark.parametrize("aa", [False, True])
-@pytest.mark.parametrize("dims", [[(48, 40, 1)], [(365, 319, 1)], [(466, 250, 1)], [(467, 250, 1)], [(700, 401, 1)],
+@pytest.mark.parametrize("dims", [[(48, 40, 1)], [(365, 319, 1)], [(483, 482, 1)], [(484, 482, 1)], [(700, 801, 1)],
                                   [(61, 53, 1), (300, 301, 1), (200, 190, 1), (400, 400, 1)]])
 def test_fields_chunks(dims, aa):
     sim = _sim(dims, aa)
