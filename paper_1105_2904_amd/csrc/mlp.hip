@@ -127,24 +127,28 @@ __global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict_
 // that owns an output tile needs no cross-wave sum at all.  The activations
 // and backward signals of every tile pass through LDS once, transposed there
 // into the operand order of the gradient products (the samples are the
-// contraction).  500 steps of 256 rows: 28.5 -> 5.8 ms (11.5 us a step: about
-// 15k cycles of tiles, 5k of products, 5k of Adam); the gradient of 44,672
+// contraction).  500 steps of 256 rows: 28.4 -> 5.2 ms (10.4 us a step: about
+// 14k cycles of tiles, 4k of products, 5k of Adam); the gradient of 44,672
 // rows on 175 workgroups 4,982 -> 22.5 us.
 // ---------------------------------------------------------------------------
 constexpr int kTiles = 16;              // tiles of a pass, and waves of the workgroup
 constexpr int kTrainThreads = 64 * kTiles;
 constexpr int kChains = 4;              // partial sums per output: tile t adds to chain t % kChains
 
-// One tile's part in the gradient products, [feature][sample].  In rows with
-// bit 3 set the two halves of the 16 samples trade places: an operand read
-// takes 4 samples of each of 16 rows, and rows r and r + 8 would start in the
-// same LDS bank.
+// One tile's part in the gradient products.  Activations and signals lie as
+// their lanes hold them, [sample][4 consecutive features], and are read back
+// with the LDS unit's transposing loads as [feature][4 consecutive samples]:
+// one 8-byte write per lane and 16 features, where writes already transposed
+// were four of 2 bytes (a training step of 256 rows 11.5 -> 10.4 us).  A sample's
+// quads of features trade places (at_quad) so that neither side meets a bank
+// conflict: a write takes one quad of each of 16 samples, a read four quads of
+// each of four.
 struct TileSignals {
-  _Float16 h1[mlp::kHid][16], h2[mlp::kHid][16];  // hidden activations
-  _Float16 g1[mlp::kHid][16], g2[mlp::kHid][16];  // dL/dz1, dL/dz2 (scaled by S)
-  _Float16 x[mlp::kIn][16];                       // inputs
-  _Float16 gy[mlp::kOut][16];                     // dL/dy (scaled by S)
-  float e[mlp::kOut][16];                         // y - t
+  h4 h1[16][mlp::kHid / 4], h2[16][mlp::kHid / 4];  // hidden activations
+  h4 g1[16][mlp::kHid / 4], g2[16][mlp::kHid / 4];  // dL/dz1, dL/dz2 (scaled by S)
+  _Float16 x[mlp::kIn][16];                         // inputs, [feature][sample]
+  _Float16 gy[mlp::kOut][16];                       // dL/dy (scaled by S)
+  float e[mlp::kOut][16];                           // y - t
 };
 struct TrainShared {
   mlp::Weights w;
@@ -152,16 +156,33 @@ struct TrainShared {
 };
 static_assert(sizeof(TrainShared) <= 160 * 1024, "one workgroup's LDS");
 
-// Place of sample j (or of the quad of samples 4q) in row `row`.
-__device__ __forceinline__ int at_sample(int row, int j) { return j ^ (row & 8); }
+// Place of feature quad q in sample s's row.
+__device__ __forceinline__ int at_quad(int s, int q) { return q ^ (4 * ((s >> 1) & 3) + 2 * (s >> 3)); }
 
-// A tile in accumulator layout (lane l: M[4(l/16)+i][l%16]) into rows
-// 16 mt .. 16 mt + 15 of a [feature][sample] array; read back four samples at
-// a time, it is the operand of the products over samples.
-__device__ __forceinline__ void put_tile(_Float16 (*dst)[16], int mt, h4 v, int lane) {
-  const int r = lane & 15, g = lane >> 4, at = at_sample(4 * g, r);
-#pragma unroll
-  for (int i = 0; i < 4; i++) dst[16 * mt + 4 * g + i][at] = v[i];
+// A tile in accumulator layout (lane l: features 16 mt + 4 (l/16) + i of sample l%16).
+__device__ __forceinline__ void put_tile(h4 (*dst)[mlp::kHid / 4], int mt, h4 v, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  dst[r][at_quad(r, 4 * mt + g)] = v;
+}
+// A transposing read: the lanes of each 16-lane group read 16 quads, lane c the
+// one at src; lane m gets element m%4 of the quads read by lanes m/4, 4 + m/4,
+// 8 + m/4 and 12 + m/4.
+__device__ __forceinline__ h4 read_transposed(const h4* src) {
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s4 lds4;
+  return __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)src));
+}
+// What lane l reads (as an index into an array's quads) so that it gets
+// features 16 mt + l%16 of samples 4 (l/16) .. + 3, an operand of the products
+// over samples.
+__device__ __forceinline__ int operand_quad(int mt, int lane) {
+  const int s = 4 * (lane >> 4) + ((lane & 15) >> 2);
+  return s * (mlp::kHid / 4) + at_quad(s, 4 * mt + (lane & 3));
+}
+// And so that it gets feature 4 q + l%4 of samples 4 ((l/4)%4) .. + 3.
+__device__ __forceinline__ int bias_quad(int q, int lane) {
+  const int s = 4 * (lane & 3) + ((lane & 15) >> 2);
+  return s * (mlp::kHid / 4) + at_quad(s, q);
 }
 
 // The inputs and targets of one tile's rows as the lanes of its wave hold
@@ -183,6 +204,20 @@ __device__ __forceinline__ TileRows load_rows(const float* __restrict__ X, const
     v.t[1] = T[row * mlp::kOut + 1];
   }
   return v;
+}
+
+// a b rounded to FP16 once (a fused multiply-add to half precision; adding
+// zero keeps the compiler from rounding the product to FP32 first).
+__device__ __forceinline__ _Float16 half_product(float a, float b) { return (_Float16)__builtin_fmaf(a, b, 0.0f); }
+// a b rounded to FP32 and then to FP16 (the empty statement keeps the compiler
+// from fusing the two).  The error signals of the second layer are rounded this
+// way where they feed the first layer's and once where they are summed: both
+// are results of half an ulp, and a training run keeps its every bit only as
+// long as each stays where it is.
+__device__ __forceinline__ _Float16 float_product(float a, float b) {
+  float p = a * b;
+  asm volatile("" : "+v"(p));
+  return (_Float16)p;
 }
 
 // Forward, loss and backward of one tile; its signals to `ts`.
@@ -222,12 +257,15 @@ __device__ __forceinline__ void tile_signals(const mlp::Weights& w, TileSignals&
   for (int mt = 0; mt < 4; mt++) {
     f4 acc = {0.f, 0.f, 0.f, 0.f};
     acc = mlp::mma(mlp::ld4(&w.w3[16 * mt + r][4 * g]), gy, acc);
+    h4 sum;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       const float hv = (float)h2[mt][i];
-      gz2[mt][i] = (_Float16)(acc[i] * (1.0f - hv * hv));
+      const float slope = 1.0f - hv * hv;
+      gz2[mt][i] = float_product(acc[i], slope);
+      sum[i] = half_product(acc[i], slope);
     }
-    put_tile(ts.g2, mt, gz2[mt], lane);
+    put_tile(ts.g2, mt, sum, lane);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
@@ -239,7 +277,7 @@ __device__ __forceinline__ void tile_signals(const mlp::Weights& w, TileSignals&
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       const float hv = (float)h1[mt][i];
-      gz1[i] = (_Float16)(acc[i] * (1.0f - hv * hv));
+      gz1[i] = half_product(acc[i], 1.0f - hv * hv);
     }
     put_tile(ts.g1, mt, gz1, lane);
     __builtin_amdgcn_sched_barrier(0);
@@ -252,7 +290,7 @@ __device__ __forceinline__ void tile_signals(const mlp::Weights& w, TileSignals&
 struct GradSums {
   f4 w2[kChains], w13[kChains];
 };
-// Bias sums: lane = 16 chain + 4 feature + quad of a wave sums, over the tiles
+// Bias sums: lane = 16 chain + 4 quad + feature of a wave sums, over the tiles
 // of its chain, samples 4 quad .. 4 quad + 3 of bias feature 64 layer +
 // 4 wave + feature (layer 0: b1, layer 1: b2); wave 8 also b3 and the loss.
 struct BiasSums {
@@ -269,28 +307,28 @@ __device__ __forceinline__ void add_tiles(const TrainShared& sh, int nt, int wv,
   const int r = lane & 15, g = lane >> 4;
   const int mt = wv >> 2, kt = wv & 3;
   const h4 zero = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
-  const int row = at_sample(r, 4 * g);  // this lane's quad in rows 16 k + r
-  const int ch = lane >> 4, fe = (lane >> 2) & 3, q = lane & 3;
-  const int fr = 4 * wv + fe, fq = at_sample(fr, 4 * q);
+  const int qa = operand_quad(mt, lane), qb = operand_quad(kt, lane), qw = operand_quad(wv & 3, lane);
+  const int ch = lane >> 4, q = (lane >> 2) & 3, fe = lane & 3;
+  const int qf = bias_quad(wv, lane);
 #pragma unroll 1
   for (int t0 = 0; t0 < nt; t0 += kChains) {
     const TileSignals* ts = sh.t + t0;
     const TileSignals& tb = ts[ch];
-    const h4 b1 = mlp::ld4(&tb.g1[fr][fq]), b2 = mlp::ld4(&tb.g2[fr][fq]);
+    const h4 b1 = read_transposed(&tb.g1[0][qf]), b2 = read_transposed(&tb.g2[0][qf]);
 #pragma unroll
     for (int c = 0; c < kChains; c++)
-      s.w2[c] = mlp::mma(mlp::ld4(&ts[c].g2[16 * mt + r][row]), mlp::ld4(&ts[c].h1[16 * kt + r][row]), s.w2[c]);
+      s.w2[c] = mlp::mma(read_transposed(&ts[c].g2[0][qa]), read_transposed(&ts[c].h1[0][qb]), s.w2[c]);
     if (wv < 4) {
 #pragma unroll
       for (int c = 0; c < kChains; c++) {
         const h4 x = mlp::ld4(&ts[c].x[r & 7][4 * g]);
-        s.w13[c] = mlp::mma(mlp::ld4(&ts[c].g1[16 * wv + r][row]), r < mlp::kIn ? x : zero, s.w13[c]);
+        s.w13[c] = mlp::mma(read_transposed(&ts[c].g1[0][qw]), r < mlp::kIn ? x : zero, s.w13[c]);
       }
     } else if (wv < 8) {
 #pragma unroll
       for (int c = 0; c < kChains; c++) {
         const h4 gy = mlp::ld4(&ts[c].gy[r & 1][4 * g]);
-        s.w13[c] = mlp::mma(r < mlp::kOut ? gy : zero, mlp::ld4(&ts[c].h2[16 * (wv - 4) + r][row]), s.w13[c]);
+        s.w13[c] = mlp::mma(r < mlp::kOut ? gy : zero, read_transposed(&ts[c].h2[0][qw]), s.w13[c]);
       }
     } else if (wv == 8) {
       b.b3 += widen(mlp::ld4(&tb.gy[fe & 1][4 * q]));  // features 0 and 1; the rest is not used
@@ -316,7 +354,7 @@ __device__ __forceinline__ float chain_sum(const f4 (&s)[kChains], int i) {
 // gets it.
 __device__ __forceinline__ float sample_sum(f4 v, int lane) {
 #pragma unroll
-  for (int o = 2; o > 0; o >>= 1)
+  for (int o = 8; o > 2; o >>= 1)
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] += __shfl_xor(v[k], o);
   const float s = (v[0] + v[2]) + (v[1] + v[3]);
@@ -330,7 +368,8 @@ __device__ __forceinline__ float sample_sum(f4 v, int lane) {
 // from w2; four consecutive columns of a W1 row (waves 0..3, r < 8) or the two
 // columns of a W3 row (waves 4..7, g = 0) from w13, n13 of them; and one bias
 // (b, -1 for none): in the lanes of chain 0, quad 0 of a feature holds its b1,
-// quad 1 its b2, and in wave 8 quad 2 of the first two features b3.
+// quad 1 its b2, and in wave 8 quad 2 of the first two features b3 (lane =
+// 16 chain + 4 quad + feature).
 struct Owned {
   int w2, w13, n13, b;
 };
@@ -340,7 +379,7 @@ __device__ __forceinline__ Owned owned_params(int wv, int lane) {
   o.w2 = mlp::oW2 + (16 * (wv & 3) + r) * mlp::kHid + 16 * (wv >> 2) + 4 * g;
   o.w13 = wv < 4 ? mlp::oW1 + r * mlp::kHid + 16 * wv + 4 * g : mlp::oW3 + (16 * (wv & 3) + r) * mlp::kOut;
   o.n13 = wv < 4 ? (r < mlp::kIn ? 4 : 0) : (wv < 8 && g == 0 ? mlp::kOut : 0);
-  const int fe = lane >> 2, q = lane & 3;
+  const int q = lane >> 2, fe = lane & 3;
   o.b = -1;
   if (lane < 16) {
     if (q == 0) o.b = mlp::oB1 + 4 * wv + fe;
@@ -354,7 +393,7 @@ __device__ __forceinline__ Owned owned_params(int wv, int lane) {
 __device__ __forceinline__ float bias_sum(const BiasSums& bs, int wv, int lane) {
   const float s1 = sample_sum(bs.b[0], lane), s2 = sample_sum(bs.b[1], lane);
   const float s3 = wv == 8 ? sample_sum(bs.b3, lane) : 0.f;
-  const int q = lane & 3;
+  const int q = (lane >> 2) & 3;
   return q == 0 ? s1 : q == 1 ? s2 : s3;
 }
 
@@ -495,8 +534,9 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
     const float db = bias_sum(bs, wv, lane);
     if (own.b >= 0) {
       adam(sb, unscale(db), as);
-      float* const dst = (lane & 3) == 0 ? sh.w.b1 : (lane & 3) == 1 ? sh.w.b2 : sh.w.b3;
-      dst[(lane & 3) == 2 ? lane >> 2 : 4 * wv + (lane >> 2)] = sb.p;
+      const int q = lane >> 2, fe = lane & 3;
+      float* const dst = q == 0 ? sh.w.b1 : q == 1 ? sh.w.b2 : sh.w.b3;
+      dst[q == 2 ? fe : 4 * wv + fe] = sb.p;
     }
     __syncthreads();
   }
