@@ -229,8 +229,10 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
  * can stream faster: fewer DRAM rows open at once.  With FP16/BF16 storage,
  * two arrays and nx a multiple of 64 above 64 the one-box kernel takes two
  * sites per lane (one 64-wide wave per 128 sites of a row, four waves to a
- * workgroup).  Every shape computes the same values bit for bit.  Defaults: width 0 (one box) or
- * 128, grid 0, no cap. */
+ * workgroup).  Every shape computes the same values bit for bit.  Defaults:
+ * width 0 (one box) or 128, grid 0, no cap (0); a context whose shape was never
+ * set caps large 3D boxes of FP32 or FP64 storage by itself, which changes no
+ * value and no reported shape. */
 int lbm_set_sweep_config(lbm_ctx* ctx, int32_t width, int32_t grid, int32_t blocks_per_cu);
 int lbm_get_sweep_config(lbm_ctx* ctx, int32_t* width, int32_t* grid, int32_t* blocks_per_cu);
 

@@ -2832,6 +2832,7 @@ struct lbm_ctx {
   int tiles_w;              // tile width the table was built for (0: none)
   int sweep_w, sweep_grid;  // sweep launch shape: w = 0 the one-box kernel, else tile width; grid 0 = one per tile
   int sweep_occ;            // cap on resident sweep workgroups per CU (0: none)
+  bool shape_set;           // a caller or a tuner set the launch shape (else sweep_cap picks the cap)
   int lds_cu, lds_block;    // LDS bytes per CU and the most one workgroup may reserve
   int device;               // the device the context was created on
   bool row_ok;              // one box whose ny and nz fit a launch grid: width 0 covers it
@@ -3055,6 +3056,20 @@ bool occ_ok(const lbm_ctx* c, int occ) {
   return occ == 0 || (occ > 0 && occ <= 32 && sweep_lds(c, occ) >= 1024 && sweep_lds(c, occ) <= (size_t)c->lds_block);
 }
 
+// Cap of a context's sweep launch.  Where none was ever set, 3D boxes of
+// workgroups of 256 take 5 in FP32 and, from 400,000 sites on, 3 in FP64: with
+// fewer resident waves fewer DRAM rows are open at once.  Steps, no cap against
+// this one: FP32 256^3 488.6 / 453.0 us, 192^3 199.9 / 189.1, 191 x 157 x 173
+// 157.4 / 153.7, 125 x 127 x 131 70.0 / 68.2, 48^3 18.95 / 18.91; FP64 192 x 160
+// x 160 265.9 / 254.4, 80^3 43.7 / 42.0, but 72^3 38.4 / 38.2 and 64^3 28.2 /
+// 29.0.  16-bit sweeps, which issue instructions more than they wait, and 2D
+// boxes lose under any cap (odd FP16 box 86.6 / 90.0 us at 5, 1024^2 30.6 / 31.2).
+int sweep_cap(const lbm_ctx* c) {
+  if (c->shape_set || c->nbox > 1 || c->dim == 2 || c->G.N < 128 * kSweepBlock) return c->sweep_occ;
+  const int cap = c->prm.storage == LBM_FP32 ? 5 : c->prm.storage == LBM_FP64 && c->G.N >= 400000 ? 3 : 0;
+  return occ_ok(c, cap) ? cap : 0;
+}
+
 template <int Q, typename T, int LAY>
 int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
   using C = typename Store<T>::C;
@@ -3137,7 +3152,7 @@ int launch_step(lbm_ctx* c) {
     }
     HIP_TRY(hipEventRecord(c->ev[c->ev_used], c->stream));
   }
-  const int rc = launch_sweep<Q, T>(c, c->sweep_w, c->sweep_grid, c->sweep_occ);
+  const int rc = launch_sweep<Q, T>(c, c->sweep_w, c->sweep_grid, sweep_cap(c));
   if (rc != LBM_OK) return rc;
   if (c->prof) {
     HIP_TRY(hipEventRecord(c->ev[c->ev_used + 1], c->stream));
@@ -3836,7 +3851,7 @@ int lbm_ensemble_add_particles(lbm_ctx* c, int32_t box, int32_t n, const double*
 // particle set, the buffer roles or the sweep launch shape changed.
 static int ensure_graph(lbm_ctx* c) {
   if (c->gexec && c->g_steps == c->graph_steps && c->g_cur == c->cur && c->g_np == c->np &&
-      c->g_nent == c->nent && c->g_w == c->sweep_w && c->g_grid == c->sweep_grid && c->g_occ == c->sweep_occ)
+      c->g_nent == c->nent && c->g_w == c->sweep_w && c->g_grid == c->sweep_grid && c->g_occ == sweep_cap(c))
     return LBM_OK;
   drop_graph(c);
   if (!c->cap) HIP_TRY(hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
@@ -3867,7 +3882,7 @@ static int ensure_graph(lbm_ctx* c) {
   c->g_nent = c->nent;
   c->g_w = c->sweep_w;
   c->g_grid = c->sweep_grid;
-  c->g_occ = c->sweep_occ;
+  c->g_occ = sweep_cap(c);
   return LBM_OK;
 }
 
@@ -3943,6 +3958,7 @@ int lbm_set_sweep_config(lbm_ctx* c, int32_t width, int32_t grid, int32_t blocks
   c->sweep_w = width;
   c->sweep_grid = tile_width(width) ? grid : 0;
   c->sweep_occ = blocks_per_cu;
+  c->shape_set = true;
   return LBM_OK;
 }
 

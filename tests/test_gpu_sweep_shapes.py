@@ -48,6 +48,36 @@ def test_one_box_sweep_equals_tiles(q, box, storage, aa):
                 assert np.array_equal(x, y), (q, box, storage, aa, walls, shape)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("aa", [False, True])
+@pytest.mark.parametrize("storage,box", [("fp32", (32, 32, 32)), ("fp32", (31, 33, 32)), ("fp32", (45, 47, 49)),
+                                         ("fp64", (74, 73, 74)), ("fp64", (75, 73, 74))])
+def test_launch_never_set_equals_a_set_one(storage, box, aa):
+    """The cap that a context picks by itself (below and above the sizes where
+    it does) changes no value and no reported shape, also where a shape is set
+    after a step graph was captured."""
+    w = [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12
+    f0 = wl.random_populations(w, (box[2], box[1], box[0]), 6, 0.01)
+    m, inertia = wl.solid_body(3, np.array([3.4]), 3.0)
+    out = []
+    for shapes in ((None, None), ((0, 0, 0), (0, 0, 0)), (None, (0, 0, 0)), (None, (0, 0, 5))):
+        sim = lbm.Simulation(19, *box, tau=0.7, storage=storage, max_particles=1, max_radius=3.4, aa=aa)
+        sim.set_distributions(f0)
+        sim.add_particles([[box[0] - 0.4, 0.3, 5.0]], u=[[0.05, 0.03, 0.04]], radius=3.4, mass=m, inertia=inertia)
+        sim.set_graph(2)
+        for shape in shapes:
+            if shape is None:
+                assert sim.sweep_config() == (0, 0, 0)
+            else:
+                sim.set_sweep_config(*shape)
+            sim.step(5)
+        out.append([sim.get_distributions()] + list(sim.forces()))
+        sim.close()
+    for o in out[1:]:
+        for x, y in zip(out[0], o):
+            assert np.array_equal(x, y), (storage, box, aa)
+
+
 def test_division_by_multiplication_is_exact():
     """n / d as (n ceil(2^sh / d)) >> sh, sh = 31 + ceil(log2 d), for
     0 <= n < 2^31: the multiplier fits 32 bits and the quotient is exact."""
