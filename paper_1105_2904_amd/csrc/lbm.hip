@@ -397,15 +397,20 @@ __host__ __device__ __forceinline__ int64_t pop_elem(int q, int i, int64_t s) {
   return (s / kPopBlock) * ((int64_t)q * kPopBlock) + (int64_t)i * kPopBlock + s % kPopBlock;
 }
 // Address of f_i at `site` (the sweep's form): the block's byte offset from
-// one 32 x 32 -> 64-bit product plus a 32-bit offset within the block.
-template <int Q, typename T>
+// one 32 x 32 -> 64-bit product plus a 32-bit offset within the block; NEAR,
+// for an array below 4 GiB, a 32-bit byte offset from f_i's first value.
+template <int Q, typename T, bool NEAR = false>
 __device__ __forceinline__ T* pop_at(T* p, int i, int site) {
+  if constexpr (NEAR)
+    return (T*)((char*)p + (size_t)i * (kPopBlock * sizeof(T)) +
+                ((uint32_t)site / kPopBlock * (uint32_t)((Q - 1) * kPopBlock * sizeof(T)) +
+                 (uint32_t)site * (uint32_t)sizeof(T)));
   return (T*)((char*)p + (size_t)((uint32_t)site / kPopBlock) * (size_t)(Q * kPopBlock * sizeof(T)) +
               (uint32_t)(i * kPopBlock + (int)((uint32_t)site % kPopBlock)) * (uint32_t)sizeof(T));
 }
-template <int Q, typename T>
+template <int Q, typename T, bool NEAR = false>
 __device__ __forceinline__ const T* pop_at(const T* p, int i, int site) {
-  return pop_at<Q, T>(const_cast<T*>(p), i, site);
+  return pop_at<Q, T, NEAR>(const_cast<T*>(p), i, site);
 }
 
 // 1/rho: the hardware reciprocal in FP32 (1 ulp), a division in FP64.
@@ -684,7 +689,7 @@ __device__ __forceinline__ void collide_site(typename Store<T>::C (&g)[Q],
 // (non-temporal) population loads.  Each pulled value is read once, so on
 // long rows they only keep dead lines out of the caches; in an ensemble of
 // narrow boxes the lines shared by neighbouring tiles are worth keeping.
-template <int Q, typename T, bool PART, int LAY, bool NTL>
+template <int Q, typename T, bool PART, int LAY, bool NTL, bool NEAR = false>
 __device__ __forceinline__ void sweep_site(const T* A, T* B, const SweepArgs<Q, typename Store<T>::C>& a,
                                            const SiteArgs<T>& sa, int x, int y, int z, int nx, int ny, int nz,
                                            int off, const typename Store<T>::C (&fbt)[Q]) {
@@ -708,7 +713,7 @@ __device__ __forceinline__ void sweep_site(const T* A, T* B, const SweepArgs<Q, 
     const int sx = LAY == kLayAAStream ? x : (L::cx(i) > 0 ? xm : (L::cx(i) < 0 ? xp : x));
     const int sy = LAY == kLayAAStream ? y : (L::cy(i) > 0 ? ym : (L::cy(i) < 0 ? yp : y));
     const int sz = LAY == kLayAAStream ? z : (L::cz(i) > 0 ? zm : (L::cz(i) < 0 ? zp : z));
-    const T* src = pop_at<Q, T>(A, LAY == kLayAASwap ? opposite<Q>(i) : i, off + sx + nx * (sy + ny * sz));
+    const T* src = pop_at<Q, T, NEAR>(A, LAY == kLayAASwap ? opposite<Q>(i) : i, off + sx + nx * (sy + ny * sz));
     const C h = NTL ? Store<T>::ldnt(src) : Store<T>::ld(src);
     g[i] = kRaw ? h : h * (C)pop_unit<T>(L::w(i));
   }
@@ -721,7 +726,7 @@ __device__ __forceinline__ void sweep_site(const T* A, T* B, const SweepArgs<Q, 
     const int dx = LAY == kLayAASwap ? (L::cx(i) > 0 ? xp : (L::cx(i) < 0 ? xm : x)) : x;
     const int dy = LAY == kLayAASwap ? (L::cy(i) > 0 ? yp : (L::cy(i) < 0 ? ym : y)) : y;
     const int dz = LAY == kLayAASwap ? (L::cz(i) > 0 ? zp : (L::cz(i) < 0 ? zm : z)) : z;
-    T* dst = pop_at<Q, T>(B, LAY == kLayAAStream ? opposite<Q>(i) : i, off + dx + nx * (dy + ny * dz));
+    T* dst = pop_at<Q, T, NEAR>(B, LAY == kLayAAStream ? opposite<Q>(i) : i, off + dx + nx * (dy + ny * dz));
     if constexpr (kRaw)
       Store<T>::st(dst, g[i]);
     else
@@ -751,24 +756,40 @@ __device__ __forceinline__ int xcd_grouped(int b, int nblocks) {
 // them to stay (FP32 191-site rows 158 us, 171 streaming) and gives runs of
 // neighbours one XCD's L2 (BF16 92.3 -> 89.6 us, FP16 90.7 -> 86.9, FP32 the
 // same).
-template <int Q, typename T, bool PART, int LAY, bool NTL>
+template <int Q, typename T, bool PART, int LAY, bool NTL, bool NEAR>
 __device__ __forceinline__ void sweep_run(int wg, const T* A, T* B, const SweepArgs<Q, typename Store<T>::C>& a,
                                           const SiteArgs<T>& sa) {
   const int lin = (int)((unsigned)wg * blockDim.x + threadIdx.x);
   if (lin >= a.n) return;
   const int row = div_by(lin, a.by_nx);
   const int z = Q == 9 ? 0 : div_by(row, a.by_ny);
-  sweep_site<Q, T, PART, LAY, NTL>(A, B, a, sa, lin - row * a.nx, row - z * a.ny, z, a.nx, a.ny, a.nz, 0, a.fbt);
+  sweep_site<Q, T, PART, LAY, NTL, NEAR>(A, B, a, sa, lin - row * a.nx, row - z * a.ny, z, a.nx, a.ny, a.nz, 0, a.fbt);
 }
+// The push half of the AA pattern with 16-bit storage is short of waves: it
+// keeps the address of every population from its load to its store.  32-bit
+// offsets (an array below 4 GiB; k_sweep_wide above) take 94 registers instead
+// of 132, so five waves fit a SIMD instead of three: BF16 191 x 157 x 173 step
+// 89.4 -> 85.1 us, 256^3 233.8 -> 229.1, FP16 234.0 -> 230.3.  The other sweeps
+// keep 64-bit addresses: with more waves they open more DRAM rows (FP32 256^3
+// step 447.9 us, 453.9 with 32-bit offsets; FP32 in one array 173.4 / 178.7; the
+// half of 16-bit storage that stays at its own sites 61.6 / 63.2).
+template <typename T, int LAY>
+constexpr bool kNearSweep = sizeof(T) == 2 && LAY == kLayAASwap;
 template <int Q, typename T, bool PART, int LAY>
 __global__ __launch_bounds__(kSweepBlock) void k_sweep(const T* A, T* B, SweepArgs<Q, typename Store<T>::C> a,
                                                         SiteArgs<T> sa) {
-  sweep_run<Q, T, PART, LAY, true>((int)blockIdx.x, A, B, a, sa);
+  sweep_run<Q, T, PART, LAY, true, kNearSweep<T, LAY>>((int)blockIdx.x, A, B, a, sa);
 }
 template <int Q, typename T, bool PART, int LAY>
 __global__ __launch_bounds__(kSweepBlock) void k_sweep_cached(const T* A, T* B, SweepArgs<Q, typename Store<T>::C> a,
                                                                SiteArgs<T> sa) {
-  sweep_run<Q, T, PART, LAY, false>(xcd_grouped((int)blockIdx.x, (int)gridDim.x), A, B, a, sa);
+  sweep_run<Q, T, PART, LAY, false, kNearSweep<T, LAY>>(xcd_grouped((int)blockIdx.x, (int)gridDim.x), A, B, a, sa);
+}
+template <int Q, typename T, bool PART, int LAY, bool NTL>
+__global__ __launch_bounds__(kSweepBlock) void k_sweep_wide(const T* A, T* B, SweepArgs<Q, typename Store<T>::C> a,
+                                                             SiteArgs<T> sa) {
+  sweep_run<Q, T, PART, LAY, NTL, false>(NTL ? (int)blockIdx.x : xcd_grouped((int)blockIdx.x, (int)gridDim.x), A, B, a,
+                                         sa);
 }
 
 // 16-bit storage, two arrays, rows of whole cache lines (nx a multiple of 64)
@@ -3102,6 +3123,15 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
     // wide workgroups (191-site rows FP32 158 us, 169 with 64 threads)
     const int block = a.n < 128 * kSweepBlock ? 64 : kSweepBlock;
     const unsigned g = blocks_for(a.n, block);
+    if constexpr (kNearSweep<T, LAY>) {
+      if ((size_t)Q * c->PS * sizeof(T) > 0xffffffffu) {
+        auto* kernel = lines ? (c->np > 0 ? k_sweep_wide<Q, T, true, LAY, true> : k_sweep_wide<Q, T, false, LAY, true>)
+                             : (c->np > 0 ? k_sweep_wide<Q, T, true, LAY, false> : k_sweep_wide<Q, T, false, LAY, false>);
+        kernel<<<g, block, lds, c->stream>>>(A, B, a, sa);
+        HIP_TRY(hipGetLastError());
+        return LBM_OK;
+      }
+    }
     if (c->np > 0 && lines)
       k_sweep<Q, T, true, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
     else if (c->np > 0)

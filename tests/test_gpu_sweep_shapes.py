@@ -78,6 +78,28 @@ def test_launch_never_set_equals_a_set_one(storage, box, aa):
             assert np.array_equal(x, y), (storage, box, aa)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("box", [(483, 483, 483), (484, 484, 485)])
+def test_push_sweep_on_both_sides_of_4_gib(box):
+    """BF16 in one array of just below and just above 4 GiB (32-bit offsets,
+    64-bit addresses) against the tile kernel: spheres at both ends of the
+    array, whose forces and motion depend on every population around them."""
+    m, inertia = wl.solid_body(3, np.array([3.4] * 3), 3.0)
+    out = []
+    for shape in ((0, 0, 0), (256, 0, 0)):
+        sim = lbm.Simulation(19, *box, tau=0.7, storage="bf16", max_particles=3, max_radius=3.4, aa=True)
+        sim.add_particles([[0.3, 0.2, box[2] - 0.6], [box[0] - 8.2, box[1] - 7.9, box[2] - 9.1], [11.0, 12.0, 10.5]],
+                          u=[[0.05, 0.03, 0.04], [-0.04, 0.05, 0.03], [0.03, -0.05, 0.04]], radius=[3.4] * 3, mass=m,
+                          inertia=inertia)
+        sim.set_sweep_config(*shape)
+        sim.step(8)
+        out.append(list(sim.forces()) + [sim.shifts()])
+        sim.close()
+    assert np.abs(out[0][0]).max() > 1e-6
+    for x, y in zip(*out):
+        assert np.array_equal(x, y), box
+
+
 def test_division_by_multiplication_is_exact():
     """n / d as (n ceil(2^sh / d)) >> sh, sh = 31 + ceil(log2 d), for
     0 <= n < 2^31: the multiplier fits 32 bits and the quotient is exact."""
