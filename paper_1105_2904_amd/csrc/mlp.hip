@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict_
 // into the operand order of the gradient products (the samples are the
 // contraction).  500 steps of 256 rows: 28.4 -> 5.2 ms (10.4 us a step: about
 // 14k cycles of tiles, 4k of products, 5k of Adam); the gradient of 44,672
-// rows on 175 workgroups 4,982 -> 22.5 us.
+// rows on 175 workgroups 4,982 -> 22.9 us.
 // ---------------------------------------------------------------------------
 constexpr int kTiles = 16;              // tiles of a pass, and waves of the workgroup
 constexpr int kTrainThreads = 64 * kTiles;
