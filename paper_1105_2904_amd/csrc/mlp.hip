@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict_
 // into the operand order of the gradient products (the samples are the
 // contraction).  500 steps of 256 rows: 28.4 -> 5.2 ms (10.4 us a step: about
 // 14k cycles of tiles, 4k of products, 5k of Adam); the gradient of 44,672
-// rows on 175 workgroups 4,982 -> 22.9 us.
+// rows on 175 workgroups 4,982 -> 21.3 us.
 // ---------------------------------------------------------------------------
 constexpr int kTiles = 16;              // tiles of a pass, and waves of the workgroup
 constexpr int kTrainThreads = 64 * kTiles;
@@ -549,23 +549,26 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
 }
 
 // Gradient sums (scaled by S) and squared errors of the rows of passes b,
-// b + gridDim.x, ... (kTiles tiles each) into row b of part: kParams values,
-// then the loss sum.  One workgroup: the finished gradient and loss instead.
+// b + gridDim.x, ... (`per` tiles each) into row b of part: kParams values,
+// then the loss sum.  WHOLE (one workgroup, passes of kTiles tiles): the
+// finished gradient and loss instead.
 constexpr int kPartStride = mlp::kParams + 2;
+template <bool WHOLE>
 __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restrict__ P, const float* __restrict__ X,
-                                                            const float* __restrict__ T, int n, float S,
+                                                            const float* __restrict__ T, int n, int tiles_per_pass, float S,
                                                             float* __restrict__ part, float* __restrict__ grad,
                                                             float* __restrict__ loss_out) {
   __shared__ TrainShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tiles = (int)(((int64_t)n + 15) / 16);
   const float Btot = (float)n;
-  const int stride = (int)gridDim.x * kTiles;
+  const int per = WHOLE ? kTiles : tiles_per_pass;
+  const int stride = (WHOLE ? 1 : (int)gridDim.x) * per;
   auto load = [&](int tile) {
     const int64_t row = (int64_t)tile * 16 + (lane & 15);
-    return load_rows(X, T, row, tile < tiles && row < n, lane);
+    return load_rows(X, T, row, wv < per && tile < tiles && row < n, lane);
   };
-  int t0 = (int)blockIdx.x * kTiles;
+  int t0 = WHOLE ? 0 : (int)blockIdx.x * per;
   TileRows next = load(t0 + wv);
   mlp::load_weights(sh.w, P, tid, kTrainThreads);
   __syncthreads();
@@ -576,15 +579,14 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restr
     const TileRows in = next;
     if (t0 + stride < tiles) next = load(t0 + stride + wv);
     // whole groups of kChains tiles: the ones past the last row add zeros
-    const int nt = min(kTiles, (tiles - t0 + kChains - 1) / kChains * kChains);
+    const int nt = min(per, (tiles - t0 + kChains - 1) / kChains * kChains);
     if (wv < nt) tile_signals(sh.w, sh.t[wv], in, (int64_t)(t0 + wv) * 16 + (lane & 15) < n, S, Btot, lane);
     __syncthreads();
     add_tiles(sh, nt, wv, lane, gs, bs);
     __syncthreads();  // the tiles are free again
   }
-  const bool whole = gridDim.x == 1;
-  float* const out = whole ? grad : part + (size_t)blockIdx.x * kPartStride;
-  const float scale = whole ? S : 1.0f;
+  float* const out = WHOLE ? grad : part + (size_t)blockIdx.x * kPartStride;
+  const float scale = WHOLE ? S : 1.0f;
   const Owned own = owned_params(wv, lane);
 #pragma unroll
   for (int i = 0; i < 4; i++) {
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restr
   if (wv == 8) {
     const float ls = sample_sum(f4{bs.loss[0], bs.loss[1], bs.loss[2], bs.loss[3]}, lane);
     if (lane == 0) {
-      if (!whole)
+      if (!WHOLE)
         out[mlp::kParams] = ls;
       else if (loss_out)
         loss_out[0] = ls / Btot;
@@ -604,16 +606,25 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restr
   }
 }
 
-// Sums of the np partial rows, in a fixed order: workgroup b takes values
-// 64 b .. 64 b + 63; its 16 waves add every 16th row each, then wave by wave.
+// Sums of the np (at most kGradMax) partial rows, in a fixed order: workgroup b
+// takes values 64 b .. 64 b + 63; its 16 waves add every 16th row each, all
+// loaded before the first addition (44,672 rows 22.9 -> 21.4 us), then wave by
+// wave.
+constexpr int kGradMax = 256;
 __global__ __launch_bounds__(1024) void k_mlp_grad_sum(const float* __restrict__ part, int np, float S, float Btot,
                                                        float* __restrict__ grad, float* __restrict__ loss_out) {
   __shared__ float s_sum[16][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int k = (int)blockIdx.x * 64 + lane;
   float v = 0.f;
-  if (k <= mlp::kParams)
-    for (int r = wv; r < np; r += 16) v += part[(size_t)r * kPartStride + k];
+  if (k <= mlp::kParams) {
+    float p[kGradMax / 16];
+#pragma unroll
+    for (int i = 0; i < kGradMax / 16; i++)
+      p[i] = wv + 16 * i < np ? part[(size_t)(wv + 16 * i) * kPartStride + k] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < kGradMax / 16; i++) v += p[i];
+  }
   s_sum[wv][lane] = v;
   __syncthreads();
   if (wv > 0 || k > mlp::kParams) return;
@@ -626,12 +637,25 @@ __global__ __launch_bounds__(1024) void k_mlp_grad_sum(const float* __restrict__
     loss_out[0] = v / Btot;
 }
 
-// Workgroups of a gradient over n rows: one per pass of kTiles tiles while
-// the chip has a CU for each (a workgroup's LDS fills one CU).
-constexpr int kGradMax = 256;
+// Tiles of a gradient's workgroup per pass: the fewest whole groups of kChains
+// with which kGradShare workgroups cover the rows, at most kTiles (then up to
+// one workgroup per CU, whose LDS it fills).  Fewer tiles share a CU's vector
+// units among fewer waves; more workgroups leave more partial rows to add.  4,
+// 8, 12, 16 tiles: 512 rows 14.3, 15.3, 16.3, 17.9 us; 8,000 16.9, 16.6, 17.7,
+// 18.5; 16,000 19.7, 18.1, 18.3, 19.2; 30,000 25.0, 20.8, 19.9, 20.5; 44,672
+// 30.3, 27.3, 22.0, 21.4.  Rows past one pass of every CU spread evenly over
+// the passes they need.
+constexpr int kGradShare = 160;
+int grad_tiles(int64_t tiles) {
+  if (tiles <= kTiles) return kTiles;
+  const int64_t passes = (tiles + kGradMax * kTiles - 1) / (kGradMax * kTiles);
+  const int64_t share = passes > 1 ? passes * kGradMax : kGradShare;
+  const int64_t per = (tiles + share - 1) / share;
+  return (int)std::min<int64_t>((per + kChains - 1) / kChains * kChains, kTiles);
+}
 int grad_groups(int32_t n) {
-  const int64_t passes = ((int64_t)n + 16 * kTiles - 1) / (16 * kTiles);
-  return (int)std::min<int64_t>(passes, kGradMax);
+  const int64_t tiles = ((int64_t)n + 15) / 16, per = grad_tiles(tiles);
+  return (int)std::min<int64_t>((tiles + per - 1) / per, kGradMax);
 }
 
 }  // namespace
@@ -660,10 +684,13 @@ int lbm_mlp_forward(const float* d_params, const float* d_x, float* d_y, int64_t
 
 static int gradient_impl(const float* d_params, const float* d_x, const float* d_t, int32_t n, float loss_scale,
                          float* d_grad, float* d_loss, float* work, int groups, hipStream_t stream) {
-  k_mlp_grad<<<groups, kTrainThreads, 0, stream>>>(d_params, d_x, d_t, n, loss_scale, work, d_grad,
-                                                                     d_loss);
-  if (groups > 1)
+  if (groups == 1) {
+    k_mlp_grad<true><<<1, kTrainThreads, 0, stream>>>(d_params, d_x, d_t, n, kTiles, loss_scale, work, d_grad, d_loss);
+  } else {
+    k_mlp_grad<false><<<groups, kTrainThreads, 0, stream>>>(d_params, d_x, d_t, n, grad_tiles(((int64_t)n + 15) / 16),
+                                                            loss_scale, work, d_grad, d_loss);
     k_mlp_grad_sum<<<(mlp::kParams + 64) / 64, 1024, 0, stream>>>(work, groups, loss_scale, (float)n, d_grad, d_loss);
+  }
   return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EHIP;
 }
 

@@ -1,6 +1,6 @@
 """The closure network's gradient and training kernels at the edges of their
-tiling: a pass is 16 tiles of 16 rows, a gradient spreads its passes over up
-to 256 workgroups (65,536 rows) and then loops, a training batch is one pass
+tiling: a pass is 4 to 16 tiles of 16 rows, a gradient spreads its passes over
+up to 256 workgroups (65,536 rows) and then loops, a training batch is one pass
 up to 256 rows and several above.
 
 Gates: those of test_gpu_mlp.py against the oracle at the same FP16 rounding
@@ -41,7 +41,7 @@ def _close(a, b, tol):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [1, 15, 16, 255, 256, 257, 4101, 65536, 65537, 70003])
+@pytest.mark.parametrize("n", [1, 15, 16, 255, 256, 257, 4101, 10240, 10241, 20481, 30721, 65536, 65537, 70003])
 def test_gradient_of_every_split(n):
     theta = _params(3)
     X, T = _data(n, 4)
