@@ -127,9 +127,9 @@ __global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict_
 // that owns an output tile needs no cross-wave sum at all.  The activations
 // and backward signals of every tile pass through LDS once, transposed there
 // into the operand order of the gradient products (the samples are the
-// contraction).  500 steps of 256 rows: 28.4 -> 5.2 ms (10.4 us a step: about
+// contraction).  500 steps of 256 rows: 28.4 -> 5.0 ms (9.9 us a step: about
 // 14k cycles of tiles, 4k of products, 5k of Adam); the gradient of 44,672
-// rows on 175 workgroups 4,982 -> 21.3 us.
+// rows on 233 workgroups 4,982 -> 17.4 us.
 // ---------------------------------------------------------------------------
 constexpr int kTiles = 16;              // tiles of a pass, and waves of the workgroup
 constexpr int kTrainThreads = 64 * kTiles;
@@ -218,6 +218,17 @@ __device__ __forceinline__ _Float16 float_product(float a, float b) {
   float p = a * b;
   asm volatile("" : "+v"(p));
   return (_Float16)p;
+}
+
+// v, of which the compiler knows nothing: what a loop derives from it (LDS
+// addresses, above all) is computed there again and not kept in registers, of
+// which sixteen waves leave each lane 128 (without it 33 loads and 9
+// stores of spilled values in a training step, now 13 in all: a step of 256
+// rows 10.3 -> 9.9 us, of 64 7.1 -> 5.6; the gradient spilled 24 and spills none
+// now: 44,672 rows 21.3 -> 17.4 us, 512 14.1 -> 11.2).
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
 }
 
 // Forward, loss and backward of one tile; its signals to `ts`.
@@ -467,11 +478,11 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
   AdamStep ahead = {};  // of step s - s % 64 + lane
   mlp::load_weights(sh.w, P, tid, kTrainThreads);
   // the row of this lane's sample in tile `tile` of the step whose first row is `from`
-  auto row_of = [&](uint32_t from, int tile) {
+  auto row_of = [&](uint32_t from, int tile, int lane) {
     return (int64_t)((from + (uint32_t)(16 * tile + (lane & 15))) % (uint32_t)n);
   };
   uint32_t base = (uint32_t)(((uint64_t)step0 * (uint32_t)batch) % (uint32_t)n);
-  TileRows next = load_rows(X, T, row_of(base, wv), wv < tiles, lane);
+  TileRows next = load_rows(X, T, row_of(base, wv, lane), wv < tiles, lane);
   __syncthreads();
   for (int s = 0; s < steps; s++) {
     GradSums gs;
@@ -483,11 +494,12 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
       // the next pass's rows, or the next step's first, load meanwhile
       const bool last = ONE || t0 + kTiles >= tiles;
       const int tn = last ? wv : t0 + kTiles + wv;
-      next = load_rows(X, T, row_of(last ? base1 : base, tn), tn < tiles, lane);
-      if (t0 + wv < tiles) tile_signals(sh.w, sh.t[wv], in, true, S, Btot, lane);
+      const int lt = fresh(lane);
+      next = load_rows(X, T, row_of(last ? base1 : base, tn, lt), tn < tiles, lt);
+      if (t0 + wv < tiles) tile_signals(sh.w, sh.t[wv], in, true, S, Btot, lt);
       __syncthreads();
       if constexpr (ONE) clear(gs, bs);
-      add_tiles(sh, min(kTiles, tiles - t0), wv, lane, gs, bs);
+      add_tiles(sh, min(kTiles, tiles - t0), wv, fresh(lane), gs, bs);
       if (last) break;
       __syncthreads();  // the tiles are free again
     }
@@ -508,7 +520,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
       return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), s % 64));
     };
     const AdamStep as = {lr, of_step(ahead.c1), of_step(ahead.c2), of_step(ahead.i1), of_step(ahead.i2)};
-    const int r = lane & 15, g = lane >> 4;
+    const int la = fresh(lane), r = la & 15, g = la >> 4;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       adam(s2[i], unscale(chain_sum(gs.w2, i)), as);
@@ -531,21 +543,22 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(float* __restrict__
         }
       }
     }
-    const float db = bias_sum(bs, wv, lane);
+    const float db = bias_sum(bs, wv, la);
     if (own.b >= 0) {
       adam(sb, unscale(db), as);
-      const int q = lane >> 2, fe = lane & 3;
+      const int q = la >> 2, fe = la & 3;
       float* const dst = q == 0 ? sh.w.b1 : q == 1 ? sh.w.b2 : sh.w.b3;
       dst[q == 2 ? fe : 4 * wv + fe] = sb.p;
     }
     __syncthreads();
   }
+  const Owned to = owned_params(wv, fresh(lane));
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    store_state(P, Mo, Vo, own.w2 + i, s2[i]);
-    if (i < own.n13) store_state(P, Mo, Vo, own.w13 + i, s13[i]);
+    store_state(P, Mo, Vo, to.w2 + i, s2[i]);
+    if (i < to.n13) store_state(P, Mo, Vo, to.w13 + i, s13[i]);
   }
-  if (own.b >= 0) store_state(P, Mo, Vo, own.b, sb);
+  if (to.b >= 0) store_state(P, Mo, Vo, to.b, sb);
 }
 
 // Gradient sums (scaled by S) and squared errors of the rows of passes b,
@@ -577,12 +590,13 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restr
   clear(gs, bs);
   for (; t0 < tiles; t0 += stride) {
     const TileRows in = next;
+    const int lt = fresh(lane);
     if (t0 + stride < tiles) next = load(t0 + stride + wv);
     // whole groups of kChains tiles: the ones past the last row add zeros
     const int nt = min(per, (tiles - t0 + kChains - 1) / kChains * kChains);
-    if (wv < nt) tile_signals(sh.w, sh.t[wv], in, (int64_t)(t0 + wv) * 16 + (lane & 15) < n, S, Btot, lane);
+    if (wv < nt) tile_signals(sh.w, sh.t[wv], in, (int64_t)(t0 + wv) * 16 + (lt & 15) < n, S, Btot, lt);
     __syncthreads();
-    add_tiles(sh, nt, wv, lane, gs, bs);
+    add_tiles(sh, nt, wv, fresh(lane), gs, bs);
     __syncthreads();  // the tiles are free again
   }
   float* const out = WHOLE ? grad : part + (size_t)blockIdx.x * kPartStride;
@@ -608,7 +622,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_grad(const float* __restr
 
 // Sums of the np (at most kGradMax) partial rows, in a fixed order: workgroup b
 // takes values 64 b .. 64 b + 63; its 16 waves add every 16th row each, all
-// loaded before the first addition (44,672 rows 22.9 -> 21.4 us), then wave by
+// loaded before the first addition (44,672 rows 22.9 -> 21.4 us at the time), then wave by
 // wave.
 constexpr int kGradMax = 256;
 __global__ __launch_bounds__(1024) void k_mlp_grad_sum(const float* __restrict__ part, int np, float S, float Btot,
@@ -641,11 +655,11 @@ __global__ __launch_bounds__(1024) void k_mlp_grad_sum(const float* __restrict__
 // with which kGradShare workgroups cover the rows, at most kTiles (then up to
 // one workgroup per CU, whose LDS it fills).  Fewer tiles share a CU's vector
 // units among fewer waves; more workgroups leave more partial rows to add.  4,
-// 8, 12, 16 tiles: 512 rows 14.3, 15.3, 16.3, 17.9 us; 8,000 16.9, 16.6, 17.7,
-// 18.5; 16,000 19.7, 18.1, 18.3, 19.2; 30,000 25.0, 20.8, 19.9, 20.5; 44,672
-// 30.3, 27.3, 22.0, 21.4.  Rows past one pass of every CU spread evenly over
+// 8, 12, 16 tiles: 512 rows 11.2, 12.2, 13.6, 15.1 us; 8,000 12.9, 13.0, 14.1,
+// 15.4; 16,000 14.8, 14.0, 14.6, 15.8; 30,000 18.5, 15.8, 16.0, 16.9; 44,672
+// 22.0, 20.9, 17.3, 17.8.  Rows past one pass of every CU spread evenly over
 // the passes they need.
-constexpr int kGradShare = 160;
+constexpr int kGradShare = 240;
 int grad_tiles(int64_t tiles) {
   if (tiles <= kTiles) return kTiles;
   const int64_t passes = (tiles + kGradMax * kTiles - 1) / (kGradMax * kTiles);

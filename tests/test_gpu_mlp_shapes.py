@@ -41,7 +41,7 @@ def _close(a, b, tol):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [1, 15, 16, 255, 256, 257, 4101, 10240, 10241, 20481, 30721, 65536, 65537, 70003])
+@pytest.mark.parametrize("n", [1, 15, 16, 255, 256, 257, 4101, 15360, 15361, 30721, 46081, 65536, 65537, 70003])
 def test_gradient_of_every_split(n):
     theta = _params(3)
     X, T = _data(n, 4)
