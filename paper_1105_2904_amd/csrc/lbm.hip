@@ -1992,13 +1992,18 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
 // finds the close pairs and runs the closure network meanwhile.  The largest
 // balls' scattered IS stores want more than one CU: those keep the separate
 // kernels (fuse_ok).  One disk in 64^2 FP64: step 14.6 -> 9.9 us; 16 boxes of
-// two disks with the closure 36.4 -> 16.1 us; one sphere in 100 x 100 x 160
+// two disks with the closure 36.4 -> 14.8 us; one sphere in 100 x 100 x 160
 // FP64 101 -> 95.5 us.
 // ---------------------------------------------------------------------------
 constexpr int kFewParticles = 4;
 constexpr int kFewPairs = kFewParticles * (kFewParticles - 1) / 2;
 constexpr int kFewTeams = 3;
 constexpr int kTeam = kBoundaryBlock;
+// With the closure a workgroup has at most two teams, so that three waves share
+// a SIMD and not four: the network then fits the registers (with three teams
+// 148 bytes a lane were spilled: 16 boxes of two disks, step 16.1 -> 14.8 us,
+// of four disks 18.8 -> 17.8).
+constexpr int few_teams(bool clo) { return clo ? 2 : kFewTeams; }
 
 // The closure in k_box (CLO: it is on).
 struct ClosureArgs {
@@ -2084,7 +2089,7 @@ struct FewOutputs {
 };
 
 template <int Q, typename T, bool NTS, bool CLO>
-__global__ __launch_bounds__(kTeam * kFewTeams + 64) void k_box(
+__global__ __launch_bounds__(kTeam * few_teams(CLO) + 64) void k_box(
     uint8_t* __restrict__ flag, typename Store<T>::C* __restrict__ vel, double* __restrict__ slot,
     const typename Store<T>::C* __restrict__ drho, T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
     double rho0, double margin, ClosureArgs clo, int lay, int* status) {
@@ -2997,7 +3002,7 @@ int launch_box(lbm_ctx* c) {
   const double margin = c->closure ? std::max(kMargin, c->clo_h) : kMargin;
   const ClosureArgs clo = {c->d_clo_packed, c->clo_h, c->prm.rho0 * (c->prm.tau - 0.5) / 3.0,
                            c->prm.tau};
-  const int block = kTeam * std::min(kFewTeams, std::max(c->box_most, c->prep_split)) + 64;
+  const int block = kTeam * std::min(few_teams(c->closure != 0), std::max(c->box_most, c->prep_split)) + 64;
   auto* kernel = streaming_is(c) ? k_box<Q, T, true, false> : k_box<Q, T, false, false>;
   if constexpr (Q == 9)
     if (c->closure) kernel = streaming_is(c) ? k_box<Q, T, true, true> : k_box<Q, T, false, true>;
