@@ -1946,9 +1946,9 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
                                                              const typename Store<T>::C* __restrict__ drho,
                                                              T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
                                                              double rho0, int pending, int lay, int split,
-                                                             int flags_all) {
+                                                             int flags_all, int first) {
   __shared__ Neighbour s_nb[kNbrMax];
-  const int p = blockIdx.x / split, part = blockIdx.x % split;
+  const int p = first + blockIdx.x / split, part = blockIdx.x % split;
   const int tid = threadIdx.x;
   const Geo G = geo_of(BX, P, p);
   Prepared a;
@@ -2960,18 +2960,23 @@ Boxes boxes_arg(const lbm_ctx* c) {
 }
 
 // The IS substep of the step that just ran (pending = 1) and the records of
-// every ball site for the next sweep.  Up to eight workgroups per particle for
-// balls of moderate size, one thread per entry otherwise.
+// the ball sites of particles first .. np - 1 for the next sweep (with an owner
+// map, which knows every claim, of all particles).  Kind grids: up to eight
+// workgroups per particle (64 for large balls); owner map: one thread per entry.
+// With kind grids the sharing lists of those particles must be of their present
+// positions: a step's k_reduce or the upload of an added box writes them just
+// before, and nothing else keeps them.
 template <int Q, typename T, bool NTS>
-int launch_prepare_as(lbm_ctx* c, int pending, int flags_all) {
+int launch_prepare_as(lbm_ctx* c, int pending, int flags_all, int first) {
   using C = typename Store<T>::C;
   if (c->grids) {
     // split workgroups per particle only while the particles alone leave the
     // GPU short of workgroups (about 8 per CU)
-    const int split = std::max(1, std::min(c->prep_split, 2048 / std::max(c->np, 1)));
-    k_prepare_grid<Q, T, NTS><<<c->np * split, kGridBlock, 0, c->stream>>>(
+    const int n = c->np - first;
+    const int split = std::max(1, std::min(c->prep_split, 2048 / std::max(n, 1)));
+    k_prepare_grid<Q, T, NTS><<<n * split, kGridBlock, 0, c->stream>>>(
         c->flag, (C*)c->vel, c->slot, (const C*)c->drho, (T*)c->f[c->cur], c->P, c->E, boxes_arg(c), c->prm.rho0,
-        pending, state_layout(c), split, flags_all);
+        pending, state_layout(c), split, flags_all, first);
   } else {
     k_prepare<Q, T, NTS><<<blocks_for(c->nent), 256, 0, c->stream>>>(
         c->own, c->flag, (C*)c->vel, c->slot, (const C*)c->drho, (T*)c->f[c->cur], c->P, c->E, boxes_arg(c),
@@ -2991,10 +2996,10 @@ bool streaming_is(const lbm_ctx* c) {
 }
 
 template <int Q, typename T>
-int launch_prepare(lbm_ctx* c, int pending, int flags_all) {
+int launch_prepare(lbm_ctx* c, int pending, int flags_all, int first) {
   if (c->nent == 0) return LBM_OK;
-  return streaming_is(c) ? launch_prepare_as<Q, T, true>(c, pending, flags_all)
-                         : launch_prepare_as<Q, T, false>(c, pending, flags_all);
+  return streaming_is(c) ? launch_prepare_as<Q, T, true>(c, pending, flags_all, first)
+                         : launch_prepare_as<Q, T, false>(c, pending, flags_all, first);
 }
 
 // The particles' part of a step of boxes with few particles (fuse_ok); c->cur
@@ -3234,7 +3239,7 @@ int launch_step(lbm_ctx* c) {
     HIP_TRY(hipGetLastError());
   }
   c->cur = 1 - c->cur;  // f[cur] now holds this step's post-collision state
-  if (c->np > 0) return launch_prepare<Q, T>(c, 1, 0);
+  if (c->np > 0) return launch_prepare<Q, T>(c, 1, 0, 0);
   return LBM_OK;
 }
 
@@ -3832,8 +3837,10 @@ static int add_impl(lbm_ctx* c, int32_t bx, int32_t n, const double* x, const do
   }
   c->nent = e1;
   c->np += n;
-  // flags and records of every ball site, with nothing pending
-  const int prc = DISPATCH(c, launch_prepare, c, 0, 1);
+  // flags and records of every ball site of the box, with nothing pending; the
+  // other boxes' stand as their last step or add left them (their sharing lists
+  // may be older: k_box and lbm_step_noalloc write none to the workspace)
+  const int prc = DISPATCH(c, launch_prepare, c, 0, 1, pbox0);
   if (prc != LBM_OK) return fail(prc);
   if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(LBM_EHIP);
   // fluid body force of every box: user value, plus the opposite of the
