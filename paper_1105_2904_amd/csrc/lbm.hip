@@ -2282,6 +2282,7 @@ __global__ __launch_bounds__(kTeam * few_teams(CLO) + 64) void k_box(
     for (int o = kFewParticles / 2; o > 0; o >>= 1) vmax = fmax(vmax, __shfl_xor(vmax, o));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if (lane == 0) {
       const PartView V{s_x, s_u, s_m, s_r, 1, 3, 0};
       double vseen = vmax;
