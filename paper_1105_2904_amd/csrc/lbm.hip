@@ -2922,11 +2922,25 @@ int state_layout(const lbm_ctx* c) { return c->prm.aa ? (c->cur == 0 ? kLayAAStr
 // with two disks of radius 48 (3,008) 14.4 / 16.0 us, with four of radius 24
 // (5,888) 15.9 / 15.7; 100 x 100 x 60 with one sphere of radius 7.5 (1,299)
 // 30.2 / 34.1 us, with four of radius 3 (1,808) 30.4 / 32.9, with one of 12
-// (3,793) 39.4 / 36.7 (each IS site has 19 scattered stores there).  The list
-// of close pairs has no global bound here, so with the closure on there must
-// be no more pairs than the separate kernel's list holds.
+// (3,793) 39.4 / 36.7 (each IS site has 19 scattered stores there).
+// Ensembles of small balls only while one round of workgroups holds the boxes
+// (those of more particles are larger: one of 3 or 4 to a CU): in a second round
+// the chain of a box waits for the one before it, where the separate kernels'
+// smaller workgroups fill the gaps.  Step of FP32 boxes, fused against separate:
+// 52^2 with four disks of radius 6 (79 entries each), 256 boxes 26.7 / 32.6 us,
+// 320 37.7 / 36.0, 1,024 82.3 / 76.0; with two, 512 boxes 38.7 / 41.6, 1,024
+// 71.0 / 65.3; 40^2 with one, 1,024 boxes 42.7 / 46.9, 2,048 76.4 / 76.3.  Balls
+// of many entries keep a workgroup busy: two disks of radius 12 (176), 1,024
+// boxes 114.9 / 116.1 us, of 24 (368) 272 / 286; four of 11 (160), 288 boxes 58.2
+// / 56.9; one disk of 12, 2,048 boxes 146.1 / 143.7.
+// The list of close pairs has no global bound here, so with the closure on there
+// must be no more pairs than the separate kernel's list holds.
+constexpr int kFewBoxes = 1024;
+constexpr int kBusyEntries = 170;
 bool fuse_ok(const lbm_ctx* c) {
+  const int64_t round = (int64_t)c->nbox * (c->box_most <= 2 ? c->box_most : kFewParticles);
   return c->grids && c->box_most <= kFewParticles && c->box_entries * c->box_most <= (c->dim == 2 ? 3200 : 2000) &&
+         (round <= kFewBoxes || c->box_entries >= (int64_t)kBusyEntries * std::max(c->box_most, 2)) &&
          (!c->closure || (int64_t)c->nbox * kFewPairs <= kClosurePairs);
 }
 
