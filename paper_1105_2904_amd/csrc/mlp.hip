@@ -418,11 +418,15 @@ __device__ __forceinline__ void clear(GradSums& s, BiasSums& b) {
 }
 
 // x / d for a divisor shared by many: inv is 1/d correctly rounded, and one
-// remainder step makes the quotient correctly rounded too (Markstein, IBM J.
-// Res. Dev. 34, 1990), four instructions fewer than a division.
+// remainder step corrects the quotient (Markstein, IBM J. Res. Dev. 34, 1990),
+// fewer instructions than a division.  From |x| = 2^-102 on that is the
+// correctly rounded quotient, below (the remainder is subnormal) possibly its
+// neighbour.  A quotient past the FP32 range has no remainder (infinity less
+// infinity) and is returned as it stands, as a division gives it.
 __device__ __forceinline__ float div_by(float x, float d, float inv) {
   const float q = x * inv;
-  return __builtin_fmaf(__builtin_fmaf(-q, d, x), inv, q);
+  const float r = __builtin_fmaf(__builtin_fmaf(-q, d, x), inv, q);
+  return __builtin_isinf(q) ? q : r;
 }
 // Constants of one Adam step (Kingma & Ba 2015): learning rate, the bias
 // corrections and their reciprocals.
