@@ -225,19 +225,22 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
  * the sweep workgroups resident on one compute unit at that number, through
  * LDS each workgroup reserves (floor(LDS per CU / blocks_per_cu), whole KiB;
  * LBM_EINVAL if that exceeds what one workgroup may reserve or is below
- * 1 KiB); 0 leaves residency to the register count.  Fewer resident waves
+ * 1 KiB); 0 leaves residency to the register count, except in the default
+ * launch of a 3D box (see below).  Fewer resident waves
  * can stream faster: fewer DRAM rows open at once.  With FP16/BF16 storage,
  * two arrays and nx a multiple of 64 above 64 the one-box kernel takes two
  * sites per lane (one 64-wide wave per 128 sites of a row, four waves to a
  * workgroup).  Every shape computes the same values bit for bit.  Defaults:
- * width 0 (one box) or 128, grid 0, no cap (0); a context whose shape was never
- * set caps large 3D boxes of FP32 or FP64 storage by itself, which changes no
- * value and no reported shape. */
+ * width 0 (one box) or 128, grid 0, cap 0.  Width 0 with cap 0, set or never
+ * set, runs 3D boxes of FP32 storage from 32,768 sites on with at most 5
+ * workgroups per compute unit and of FP64 storage from 400,000 sites on with at
+ * most 3 (and is reported as 0, 0, 0); a cap of 8 or more never binds there. */
 int lbm_set_sweep_config(lbm_ctx* ctx, int32_t width, int32_t grid, int32_t blocks_per_cu);
 int lbm_get_sweep_config(lbm_ctx* ctx, int32_t* width, int32_t* grid, int32_t* blocks_per_cu);
 
 /* Time every sweep shape (widths 0 (one box), 64, 128, 256, 512; grids 0 and
- * 4, 8, 16, 32 per CU; caps none, 6, 5, 4, 3, 2 workgroups per CU; reps
+ * 4, 8, 16, 32 per CU; caps 0, 6, 5, 4, 3, 2 workgroups per CU, and 8 for width
+ * 0 where the default launch has a cap of its own; reps
  * launches each, after one warm-up) on the context's own state, time the four
  * fastest again in two alternating rounds of 2 reps launches, and keep the
  * fastest of those; returns it and its time per sweep in ms (any output

@@ -2862,7 +2862,6 @@ struct lbm_ctx {
   int tiles_w;              // tile width the table was built for (0: none)
   int sweep_w, sweep_grid;  // sweep launch shape: w = 0 the one-box kernel, else tile width; grid 0 = one per tile
   int sweep_occ;            // cap on resident sweep workgroups per CU (0: none)
-  bool shape_set;           // a caller or a tuner set the launch shape (else sweep_cap picks the cap)
   int lds_cu, lds_block;    // LDS bytes per CU and the most one workgroup may reserve
   int device;               // the device the context was created on
   bool row_ok;              // one box whose ny and nz fit a launch grid: width 0 covers it
@@ -3105,16 +3104,18 @@ bool occ_ok(const lbm_ctx* c, int occ) {
   return occ == 0 || (occ > 0 && occ <= 32 && sweep_lds(c, occ) >= 1024 && sweep_lds(c, occ) <= (size_t)c->lds_block);
 }
 
-// Cap of a context's sweep launch.  Where none was ever set, 3D boxes of
-// workgroups of 256 take 5 in FP32 and, from 400,000 sites on, 3 in FP64: with
-// fewer resident waves fewer DRAM rows are open at once.  Steps, no cap against
+// Cap that the sweep launch (width w, cap occ) runs with: occ, except that the
+// default launch (width 0, no cap) of 3D boxes of 32,768 sites and more takes 5
+// in FP32 and, from 400,000 sites on, 3 in FP64: with fewer resident waves fewer
+// DRAM rows are open at once.  A rule on the launch alone, so that a launch read
+// from one context and set in another runs the same.  Steps, no cap against
 // this one: FP32 256^3 488.6 / 453.0 us, 192^3 199.9 / 189.1, 191 x 157 x 173
 // 157.4 / 153.7, 125 x 127 x 131 70.0 / 68.2, 48^3 18.95 / 18.91; FP64 192 x 160
 // x 160 265.9 / 254.4, 80^3 43.7 / 42.0, but 72^3 38.4 / 38.2 and 64^3 28.2 /
 // 29.0.  16-bit sweeps, which issue instructions more than they wait, and 2D
 // boxes lose under any cap (odd FP16 box 86.6 / 90.0 us at 5, 1024^2 30.6 / 31.2).
-int sweep_cap(const lbm_ctx* c) {
-  if (c->shape_set || c->nbox > 1 || c->dim == 2 || c->G.N < 128 * kSweepBlock) return c->sweep_occ;
+int sweep_cap(const lbm_ctx* c, int w, int occ) {
+  if (w != 0 || occ != 0 || c->dim == 2 || c->G.N < 128 * kSweepBlock) return occ;
   const int cap = c->prm.storage == LBM_FP32 ? 5 : c->prm.storage == LBM_FP64 && c->G.N >= 400000 ? 3 : 0;
   return occ_ok(c, cap) ? cap : 0;
 }
@@ -3210,7 +3211,7 @@ int launch_step(lbm_ctx* c) {
     }
     HIP_TRY(hipEventRecord(c->ev[c->ev_used], c->stream));
   }
-  const int rc = launch_sweep<Q, T>(c, c->sweep_w, c->sweep_grid, sweep_cap(c));
+  const int rc = launch_sweep<Q, T>(c, c->sweep_w, c->sweep_grid, sweep_cap(c, c->sweep_w, c->sweep_occ));
   if (rc != LBM_OK) return rc;
   if (c->prof) {
     HIP_TRY(hipEventRecord(c->ev[c->ev_used + 1], c->stream));
@@ -3911,7 +3912,7 @@ int lbm_ensemble_add_particles(lbm_ctx* c, int32_t box, int32_t n, const double*
 // particle set, the buffer roles or the sweep launch shape changed.
 static int ensure_graph(lbm_ctx* c) {
   if (c->gexec && c->g_steps == c->graph_steps && c->g_cur == c->cur && c->g_np == c->np &&
-      c->g_nent == c->nent && c->g_w == c->sweep_w && c->g_grid == c->sweep_grid && c->g_occ == sweep_cap(c))
+      c->g_nent == c->nent && c->g_w == c->sweep_w && c->g_grid == c->sweep_grid && c->g_occ == c->sweep_occ)
     return LBM_OK;
   drop_graph(c);
   if (!c->cap) HIP_TRY(hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
@@ -3942,7 +3943,7 @@ static int ensure_graph(lbm_ctx* c) {
   c->g_nent = c->nent;
   c->g_w = c->sweep_w;
   c->g_grid = c->sweep_grid;
-  c->g_occ = sweep_cap(c);
+  c->g_occ = c->sweep_occ;
   return LBM_OK;
 }
 
@@ -4018,7 +4019,6 @@ int lbm_set_sweep_config(lbm_ctx* c, int32_t width, int32_t grid, int32_t blocks
   c->sweep_w = width;
   c->sweep_grid = tile_width(width) ? grid : 0;
   c->sweep_occ = blocks_per_cu;
-  c->shape_set = true;
   return LBM_OK;
 }
 
@@ -4031,12 +4031,15 @@ int lbm_get_sweep_config(lbm_ctx* c, int32_t* width, int32_t* grid, int32_t* blo
 }
 
 // The sweep launches both tuners try: shapes x occupancy caps (fewer
-// resident waves can stream faster).
+// resident waves can stream faster).  Where the default launch has a cap of its
+// own, the one-box kernel without one is there as a cap of 8, which never binds
+// (8 workgroups of 256 are all the waves a CU holds).
 struct SweepCand {
   int w, g, occ;
 };
 static std::vector<SweepCand> sweep_candidates(const lbm_ctx* c, int ncu) {
   std::vector<SweepCand> cands;
+  if (c->row_ok && sweep_cap(c, 0, 0) != 0 && occ_ok(c, 8)) cands.push_back({0, 0, 8});
   for (int occ : {0, 6, 5, 4, 3, 2}) {
     if (!occ_ok(c, occ)) continue;
     if (c->row_ok) cands.push_back({0, 0, occ});
@@ -4066,12 +4069,13 @@ int lbm_autotune(lbm_ctx* c, int32_t reps, int32_t* width, int32_t* grid, int32_
   // time `n` sweeps of one candidate (after one untimed), in ms per sweep
   auto time_cand = [&](const Cand& cd, int n, double& ms_out) {
     if (tile_width(cd.w) && (rc = build_tiles(c, cd.w)) != LBM_OK) return false;
-    if ((rc = DISPATCH(c, launch_sweep, c, cd.w, cd.g, cd.occ)) != LBM_OK) return false;  // warm-up
+    const int occ = sweep_cap(c, cd.w, cd.occ);
+    if ((rc = DISPATCH(c, launch_sweep, c, cd.w, cd.g, occ)) != LBM_OK) return false;  // warm-up
     if (hipEventRecord(e0, c->stream) != hipSuccess) {
       rc = LBM_EHIP;
       return false;
     }
-    for (int r = 0; r < n && rc == LBM_OK; r++) rc = DISPATCH(c, launch_sweep, c, cd.w, cd.g, cd.occ);
+    for (int r = 0; r < n && rc == LBM_OK; r++) rc = DISPATCH(c, launch_sweep, c, cd.w, cd.g, occ);
     if (rc != LBM_OK) return false;
     float ms = 0;
     if (hipEventRecord(e1, c->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
