@@ -51,17 +51,17 @@ def streaming_rows(tname, nx):
 def sweep_geometry(box, launch, pairs=False):
     """Workgroup size and grid (threads) of the sweep launch (width, grid,
     blocks_per_cu) on one box: the one-box kernel (width 0) runs a thread per
-    site in workgroups of 256 (64 below 32,768 sites), or with two sites per
-    lane one 64-lane wave per 128 sites of a row, four waves to a workgroup;
-    tiles are w consecutive sites of the box, one per workgroup unless a
-    smaller persistent grid is set."""
+    site in workgroups of 256 (64 below 32,768 sites without a cap), or with
+    two sites per lane one 64-lane wave per 128 sites of a row, four waves to a
+    workgroup; tiles are w consecutive sites of the box, one per workgroup
+    unless a smaller persistent grid is set."""
     import math
     nx, ny, nz = box
     w, g = launch["width"], launch["grid"]
     if w == 0 and pairs:
         return 256, math.ceil(math.ceil(nx / 128) * ny * nz / 4) * 256
     if w == 0:
-        wg = 64 if nx * ny * nz < 32768 else 256
+        wg = 64 if nx * ny * nz < 32768 and launch["blocks_per_cu"] == 0 else 256
         return wg, math.ceil(nx * ny * nz / wg) * wg
     nt = math.ceil(nx * ny * nz / w)
     return w, (g if 0 < g < nt else nt) * w

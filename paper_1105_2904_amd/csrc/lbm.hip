@@ -3149,8 +3149,9 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
     }
     // a box of fewer than 128 workgroups of 256 spreads over more CUs in waves
     // of one (64^2 step 15.2 -> 14.7 us); larger ones share lines less with
-    // wide workgroups (191-site rows FP32 158 us, 169 with 64 threads)
-    const int block = a.n < 128 * kSweepBlock ? 64 : kSweepBlock;
+    // wide workgroups (191-site rows FP32 158 us, 169 with 64 threads).  A cap
+    // counts workgroups of 256, whatever the box.
+    const int block = a.n < 128 * kSweepBlock && occ == 0 ? 64 : kSweepBlock;
     const unsigned g = blocks_for(a.n, block);
     if constexpr (kNearSweep<T, LAY>) {
       if ((size_t)Q * c->PS * sizeof(T) > 0xffffffffu) {
