@@ -3120,6 +3120,10 @@ int sweep_cap(const lbm_ctx* c, int w, int occ) {
   return occ_ok(c, cap) ? cap : 0;
 }
 
+// Sites below which a box is too few workgroups for the rules of larger ones.
+template <typename T>
+constexpr int kSmallSweep = sizeof(T) == 2 ? 500000 : 350000;
+
 template <int Q, typename T, int LAY>
 int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
   using C = typename Store<T>::C;
@@ -3150,8 +3154,15 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
     // a box of fewer than 128 workgroups of 256 spreads over more CUs in waves
     // of one (64^2 step 15.2 -> 14.7 us); larger ones share lines less with
     // wide workgroups (191-site rows FP32 158 us, 169 with 64 threads).  A cap
-    // counts workgroups of 256, whatever the box.
-    const int block = a.n < 128 * kSweepBlock && occ == 0 ? 64 : kSweepBlock;
+    // counts workgroups of 256, whatever the box.  Whole-line rows that fit one
+    // workgroup and fill more than half of it get one each where the sweep is in
+    // place or FP32: workgroups of 256 that end within a row are slower there
+    // (FP32 in one array 224 x 200 x 200 251 -> 222 us, 192 x 56 x 56 18.2 ->
+    // 16.2; FP16 192 x 144 x 144 57.8 -> 52.9; FP32 in two 192 x 144 x 144 99.8 ->
+    // 97.3), but not in FP64 in two arrays (160 x 158 x 158 194 / 206).
+    const bool row = lines && a.n >= kSmallSweep<T> && 2 * a.nx > kSweepBlock && a.nx < kSweepBlock &&
+                     (LAY != kLayAB || sizeof(T) == 4);
+    const int block = a.n < 128 * kSweepBlock && occ == 0 ? 64 : row ? a.nx : kSweepBlock;
     const unsigned g = blocks_for(a.n, block);
     if constexpr (kNearSweep<T, LAY>) {
       if ((size_t)Q * c->PS * sizeof(T) > 0xffffffffu) {

@@ -1,0 +1,26 @@
+"""The one-box sweep (width 0) at the lines where its launch changes with row
+length and box size, against the tile kernel, bit for bit: rows of their own
+workgroup and the row lengths next to them."""
+import pytest
+
+from test_gpu_sweep_shapes import _run
+from paper_1105_2904_amd import workloads as wl
+
+import numpy as np
+
+ROWS = [("fp32", True, (224, 40, 40)), ("fp32", True, (192, 44, 43)), ("fp32", False, (160, 47, 47)), ("fp32", False, (129, 53, 53)),
+        ("fp32", True, (128, 53, 53)), ("fp32", False, (255, 38, 38)), ("fp32", True, (256, 38, 38)), ("fp64", True, (144, 50, 50)),
+        ("fp64", True, (240, 39, 39)), ("fp64", False, (208, 42, 42)), ("fp16", True, (192, 52, 52)), ("bf16", True, (192, 52, 52)),
+        ("fp32", True, (224, 40, 39)), ("fp16", True, (192, 51, 50))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,aa,box", ROWS)
+def test_rows_of_their_own_workgroup(storage, aa, box):
+    w = [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12
+    f0 = wl.random_populations(w, (box[2], box[1], box[0]), 5, 0.01)
+    for walls in (0, 7):
+        a = _run(19, box, storage, aa, walls, (0, 0, 0), f0)
+        b = _run(19, box, storage, aa, walls, (256, 0, 0), f0)
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y), (storage, aa, box, walls)
