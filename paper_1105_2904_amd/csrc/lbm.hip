@@ -755,7 +755,11 @@ __device__ __forceinline__ int xcd_grouped(int b, int nblocks) {
 // at a workgroup's ends hold its neighbours' sites too: k_sweep_cached loads
 // them to stay (FP32 191-site rows 158 us, 171 streaming) and gives runs of
 // neighbours one XCD's L2 (BF16 92.3 -> 89.6 us, FP16 90.7 -> 86.9, FP32 the
-// same).
+// same).  Small 3D boxes (kSmallSweep) in two arrays of FP64 or FP32 take
+// k_sweep whatever their rows: the runs of their few workgroups load the XCDs
+// unevenly (step with a sphere, FP64 50^3 17.8 us grouped, 15.5 streaming, 66^3
+// 27.9 / 26.0, FP32 66^3 19.3 / 17.6; but 16-bit 66^3 14.8 / 15.1, in one array
+// FP32 25.4 / 26.1, 2D FP64 300^2 11.0 / 12.1).
 template <int Q, typename T, bool PART, int LAY, bool NTL, bool NEAR>
 __device__ __forceinline__ void sweep_run(int wg, const T* A, T* B, const SweepArgs<Q, typename Store<T>::C>& a,
                                           const SiteArgs<T>& sa) {
@@ -3164,6 +3168,7 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
                      (LAY != kLayAB || sizeof(T) == 4);
     const int block = a.n < 128 * kSweepBlock && occ == 0 ? 64 : row ? a.nx : kSweepBlock;
     const unsigned g = blocks_for(a.n, block);
+    const bool streaming = lines || (Q == 19 && LAY == kLayAB && sizeof(T) > 2 && a.n < kSmallSweep<T>);
     if constexpr (kNearSweep<T, LAY>) {
       if ((size_t)Q * c->PS * sizeof(T) > 0xffffffffu) {
         auto* kernel = lines ? (c->np > 0 ? k_sweep_wide<Q, T, true, LAY, true> : k_sweep_wide<Q, T, false, LAY, true>)
@@ -3173,11 +3178,11 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
         return LBM_OK;
       }
     }
-    if (c->np > 0 && lines)
+    if (c->np > 0 && streaming)
       k_sweep<Q, T, true, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
     else if (c->np > 0)
       k_sweep_cached<Q, T, true, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
-    else if (lines)
+    else if (streaming)
       k_sweep<Q, T, false, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);
     else
       k_sweep_cached<Q, T, false, LAY><<<g, block, lds, c->stream>>>(A, B, a, sa);

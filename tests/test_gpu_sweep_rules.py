@@ -1,6 +1,7 @@
 """The one-box sweep (width 0) at the lines where its launch changes with row
 length and box size, against the tile kernel, bit for bit: rows of their own
-workgroup and the row lengths next to them."""
+workgroup and the row lengths next to them, small boxes whose workgroups are not
+grouped, and the sizes next to those."""
 import pytest
 
 from test_gpu_sweep_shapes import _run
@@ -24,3 +25,10 @@ def test_rows_of_their_own_workgroup(storage, aa, box):
         b = _run(19, box, storage, aa, walls, (256, 0, 0), f0)
         for x, y in zip(a, b):
             assert np.array_equal(x, y), (storage, aa, box, walls)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,aa,box", [("fp64", False, (70, 71, 70)), ("fp64", False, (71, 71, 70)), ("fp32", False, (70, 71, 70)),
+                                            ("fp32", False, (71, 71, 70)), ("fp32", True, (50, 51, 52)), ("fp64", False, (21, 23, 20))])
+def test_both_sides_of_a_small_box(storage, aa, box):
+    test_rows_of_their_own_workgroup(storage, aa, box)
