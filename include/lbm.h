@@ -232,7 +232,7 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
  * sites per lane (one 64-wide wave per 128 sites of a row, four waves to a
  * workgroup).  Every shape computes the same values bit for bit.  Defaults:
  * width 0 (one box) or 128, grid 0, cap 0.  Width 0 with cap 0, set or never
- * set, runs 3D boxes of FP32 storage from 32,768 sites on with at most 5
+ * set, runs 3D boxes of FP32 storage from 700,000 sites on with at most 5
  * workgroups per compute unit and of FP64 storage from 400,000 sites on with at
  * most 3 (and is reported as 0, 0, 0); a cap of 8 or more never binds there. */
 int lbm_set_sweep_config(lbm_ctx* ctx, int32_t width, int32_t grid, int32_t blocks_per_cu);

@@ -3109,18 +3109,21 @@ bool occ_ok(const lbm_ctx* c, int occ) {
 }
 
 // Cap that the sweep launch (width w, cap occ) runs with: occ, except that the
-// default launch (width 0, no cap) of 3D boxes of 32,768 sites and more takes 5
-// in FP32 and, from 400,000 sites on, 3 in FP64: with fewer resident waves fewer
-// DRAM rows are open at once.  A rule on the launch alone, so that a launch read
-// from one context and set in another runs the same.  Steps, no cap against
-// this one: FP32 256^3 488.6 / 453.0 us, 192^3 199.9 / 189.1, 191 x 157 x 173
-// 157.4 / 153.7, 125 x 127 x 131 70.0 / 68.2, 48^3 18.95 / 18.91; FP64 192 x 160
-// x 160 265.9 / 254.4, 80^3 43.7 / 42.0, but 72^3 38.4 / 38.2 and 64^3 28.2 /
-// 29.0.  16-bit sweeps, which issue instructions more than they wait, and 2D
-// boxes lose under any cap (odd FP16 box 86.6 / 90.0 us at 5, 1024^2 30.6 / 31.2).
+// default launch (width 0, no cap) of 3D boxes takes 5 in FP32 from 700,000
+// sites on and 3 in FP64 from 400,000: with fewer resident waves fewer DRAM rows
+// are open at once.  A rule on the launch alone, so that a launch read from one
+// context and set in another runs the same.  Steps, no cap against this one:
+// FP32 256^3 488.6 / 453.0 us, 192^3 199.9 / 189.1, 191 x 157 x 173 157.4 / 153.7,
+// 128 x 128 x 64 36.6 / 35.4, 96^3 39.0 / 38.2, but 80^3 25.0 / 25.4 and 256 x 64
+// x 32 22.2 / 22.7; FP64 192 x 160 x 160 265.9 / 254.4, 80^3 43.7 / 42.0, but 72^3
+// 38.4 / 38.2 and 64^3 28.2 / 29.0.  16-bit sweeps, which issue instructions more
+// than they wait, and 2D boxes lose under any cap (odd FP16 box 86.6 / 90.0 us at
+// 5, 1024^2 30.6 / 31.2).
 int sweep_cap(const lbm_ctx* c, int w, int occ) {
-  if (w != 0 || occ != 0 || c->dim == 2 || c->G.N < 128 * kSweepBlock) return occ;
-  const int cap = c->prm.storage == LBM_FP32 ? 5 : c->prm.storage == LBM_FP64 && c->G.N >= 400000 ? 3 : 0;
+  if (w != 0 || occ != 0 || c->dim == 2) return occ;
+  const int cap = c->prm.storage == LBM_FP32 && c->G.N >= 700000   ? 5
+                  : c->prm.storage == LBM_FP64 && c->G.N >= 400000 ? 3
+                                                                   : 0;
   return occ_ok(c, cap) ? cap : 0;
 }
 

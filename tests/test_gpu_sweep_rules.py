@@ -32,3 +32,15 @@ def test_rows_of_their_own_workgroup(storage, aa, box):
                                             ("fp32", False, (71, 71, 70)), ("fp32", True, (50, 51, 52)), ("fp64", False, (21, 23, 20))])
 def test_both_sides_of_a_small_box(storage, aa, box):
     test_rows_of_their_own_workgroup(storage, aa, box)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,box", [("fp32", (88, 89, 89)), ("fp32", (100, 70, 100)), ("fp32", (128, 75, 74)),
+                                         ("fp64", (74, 73, 74)), ("fp64", (74, 73, 75))])
+def test_default_cap_changes_no_value(storage, box):
+    w = [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12
+    f0 = wl.random_populations(w, (box[2], box[1], box[0]), 5, 0.01)
+    a = _run(19, box, storage, False, 0, (0, 0, 0), f0)
+    for shape in ((0, 0, 8), (0, 0, 2)):
+        for x, y in zip(a, _run(19, box, storage, False, 0, shape, f0)):
+            assert np.array_equal(x, y), (storage, box, shape)
