@@ -796,9 +796,8 @@ __global__ __launch_bounds__(kSweepBlock) void k_sweep_wide(const T* A, T* B, Sw
                                          sa);
 }
 
-// 16-bit storage, two arrays, rows of whole cache lines (nx a multiple of 64)
-// longer than a wave: two sites per lane.  A wave takes 128
-// consecutive sites of a row (64 site pairs, x even), so each population is
+// 16-bit storage, two arrays, even rows (launch_sweep_as says which): two sites
+// per lane.  A wave takes 128 consecutive sites of a row (64 site pairs, x even), so each population is
 // one aligned 4-byte load per lane, 256 bytes per wave as FP32 moves with one
 // site per lane (2-byte loads of one site per lane stream about 10 % slower).
 // The pull's shift by one site along x (populations with c_x != 0) is rebuilt
@@ -835,6 +834,7 @@ __device__ __forceinline__ uint32_t pack_halves(float lo, float hi) {
   }
 }
 constexpr int kPairRow = 128;  // sites of a row per wave of k_sweep_pairs
+constexpr int kPairWaves = 5120;  // waves of it that the GPU runs at once (five per SIMD)
 // Index of population i among those with c_x != 0 (and their count, i = Q).
 template <typename Lt>
 __host__ __device__ constexpr int x_shifted_before(int i) {
@@ -3146,9 +3146,15 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
       // two sites per lane, one wave per 128 sites of a row, while rows are
       // whole cache lines and fill a wave (FP16, 5.2 M sites, step by row
       // length, against one site per lane: 128 86.7 / 90.4 us, 192 88.1 / 93.0,
-      // 320 89.1 / 94.0; but 64 106.3 / 85.5, 250 118.7 / 91.2)
-      if (lines && a.nx > 64) {
-        const int64_t waves = (int64_t)((a.nx + kPairRow - 1) / kPairRow) * c->G.ny * c->G.nz;
+      // 320 89.1 / 94.0; but 64 106.3 / 85.5, 250 118.7 / 91.2); and in 3D boxes of
+      // 350,000 sites and more of any even row length while one round holds every
+      // wave (sweep without particles, step with 20 spheres, against one site
+      // per lane: 224 x 47 x 47 8.2 / 9.4 and 22.5 / 24.5 us, 240 x 50 x 50 10.0 /
+      // 11.0 and 23.6 / 26.0; past one round 208 x 54 x 54 11.6 / 11.1), without
+      // particles only if rows are whole 16-byte parts (350 x 38 x 38 11.5 / 9.8)
+      const int64_t waves = (int64_t)((a.nx + kPairRow - 1) / kPairRow) * c->G.ny * c->G.nz;
+      const bool round = Q == 19 && a.nx % 2 == 0 && a.n >= 350000 && waves <= kPairWaves && (c->np > 0 || a.nx % 8 == 0);
+      if ((lines && a.nx > 64) || round) {
         const unsigned g = (unsigned)((waves + kSweepBlock / 64 - 1) / (kSweepBlock / 64));
         if (c->np > 0)
           k_sweep_pairs<Q, T, true><<<g, kSweepBlock, lds, c->stream>>>(A, B, a, sa);

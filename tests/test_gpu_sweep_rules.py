@@ -44,3 +44,13 @@ def test_default_cap_changes_no_value(storage, box):
     for shape in ((0, 0, 8), (0, 0, 2)):
         for x, y in zip(a, _run(19, box, storage, False, 0, shape, f0)):
             assert np.array_equal(x, y), (storage, box, shape)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage", ["fp16", "bf16"])
+@pytest.mark.parametrize("box", [(224, 47, 47), (240, 50, 50), (250, 45, 45), (100, 71, 72), (416, 29, 30), (200, 42, 41), (200, 42, 42),
+                                 (240, 50, 51), (240, 51, 51), (82, 70, 73), (239, 47, 47)])
+def test_even_rows_with_two_sites_per_lane(storage, box):
+    """Even rows that are not whole cache lines, inside and outside of one round of
+    waves and on both sides of 350,000 sites (and an odd row)."""
+    test_rows_of_their_own_workgroup(storage, False, box)
