@@ -384,8 +384,10 @@ def mlp_gradient(params, x, t, loss_scale=1024.0, stream=None):
     nbytes = ctypes.c_size_t(0)
     _check(lib().lbm_mlp_gradient_work_size(x.shape[0], ctypes.byref(nbytes)), "lbm_mlp_gradient")
     work = torch.empty(nbytes.value // 4, dtype=torch.float32, device=params.device)
-    if stream is not None:
-        work.record_stream(stream)  # allocated on the current stream, used on this one
+    if stream:
+        # allocated on the current stream, used on this one (any object with a handle)
+        work.record_stream(stream if isinstance(stream, torch.Stream) else
+                           torch.cuda.ExternalStream(stream.cuda_stream, device=params.device))
     _check(lib().lbm_mlp_gradient_in(_ptr(params), _ptr(x), _ptr(t), x.shape[0], float(loss_scale), _ptr(g), _ptr(loss),
                                      ctypes.c_void_p(work.data_ptr()), nbytes.value, _stream(stream)),
            "lbm_mlp_gradient")
