@@ -56,7 +56,7 @@ def lib():
             "lbm_create": [P, vp, ctypes.c_size_t, vp, ctypes.POINTER(vp)],
             "lbm_add_particles": [vp, ctypes.c_int32, _dp, _dp, _dp, _dp, _dp, _dp, _ip],
             "lbm_step": [vp, ctypes.c_int32],
-            "lbm_forces": [vp, _dp, _dp, _dp, _dp, _dp],
+            "lbm_forces": [vp, vp, vp, vp, vp, vp],
             "lbm_fields": [vp, _dp, _dp, _ip],
             "lbm_destroy": [vp],
             "lbm_get_distributions": [vp, _dp],
@@ -296,10 +296,10 @@ class Simulation:
 
     def forces(self):
         n = self.n_particles
-        out = np.zeros((5, n, 3))
+        out = np.empty((5, n, 3))
         at, size = out.ctypes.data, 24 * n
-        _check(lib().lbm_forces(self.ctx, *(ctypes.cast(at + k * size, _dp) for k in range(5))), "lbm_forces")
-        return tuple(out)  # F, T, x, u, omega
+        _check(lib().lbm_forces(self.ctx, at, at + size, at + 2 * size, at + 3 * size, at + 4 * size), "lbm_forces")
+        return tuple(a.copy() for a in out)  # F, T, x, u, omega, each an array of its own
 
     def fields(self):
         rho = np.empty(self.N)
