@@ -2848,6 +2848,27 @@ class CopyTeam {
 
 }  // namespace
 
+// While it lives, the stream's device is the calling thread's current one.
+namespace {
+class StreamDevice {
+ public:
+  explicit StreamDevice(hipStream_t stream) noexcept {
+    hipDevice_t dev = 0;
+    if (!stream || hipGetDevice(&back_) != hipSuccess || hipStreamGetDevice(stream, &dev) != hipSuccess || dev == back_ ||
+        hipSetDevice(dev) != hipSuccess)
+      back_ = -1;
+  }
+  ~StreamDevice() {
+    if (back_ >= 0) (void)hipSetDevice(back_);
+  }
+  StreamDevice(const StreamDevice&) = delete;
+  StreamDevice& operator=(const StreamDevice&) = delete;
+
+ private:
+  int back_ = -1;  // the device to go back to
+};
+}  // namespace
+
 // ---------------------------------------------------------------------------
 // Context
 // ---------------------------------------------------------------------------
@@ -4333,9 +4354,12 @@ int lbm_fields(lbm_ctx* c, double* rho, double* u, int32_t* owner) {
     }
   } hb;
   bool pinned = true;
-  for (int k = 0; k < (nchunk > 1 ? 2 : 1) && pinned; k++) {
-    hb.b[k] = host_take(kSite * (size_t)chunk);
-    pinned = hb.b[k].p && hipEventCreateWithFlags(&hb.done[k], hipEventDisableTiming) == hipSuccess;
+  {
+    const StreamDevice there(c->stream);  // an event is recorded on streams of its own device only
+    for (int k = 0; k < (nchunk > 1 ? 2 : 1) && pinned; k++) {
+      hb.b[k] = host_take(kSite * (size_t)chunk);
+      pinned = hb.b[k].p && hipEventCreateWithFlags(&hb.done[k], hipEventDisableTiming) == hipSuccess;
+    }
   }
   CopyTeam team(pinned ? kSite * (size_t)c->NT : 0);
   auto fetch = [&](int64_t k) -> int {  // chunk k into block k % 2
