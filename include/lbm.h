@@ -230,7 +230,8 @@ int lbm_box_info(lbm_ctx* ctx, int32_t box, int32_t* dims, int64_t* first_site, 
  * can stream faster: fewer DRAM rows open at once.  With FP16/BF16 storage,
  * two arrays and nx a multiple of 64 above 64 (other even nx in some 3D boxes of
  * about half a million sites) the one-box kernel takes two sites per lane (one
- * 64-wide wave per 128 sites of a row, four waves to a workgroup).  Every shape computes the same values bit for bit.  Defaults:
+ * 64-wide wave per 128 sites of a row, four waves to a workgroup).  Every shape
+ * computes the same values bit for bit.  Defaults:
  * width 0 (one box) or 128, grid 0, cap 0.  Width 0 with cap 0, set or never
  * set, runs 3D boxes of FP32 storage from 700,000 sites on with at most 5
  * workgroups per compute unit and of FP64 storage from 400,000 sites on with at

@@ -755,11 +755,13 @@ __device__ __forceinline__ int xcd_grouped(int b, int nblocks) {
 // at a workgroup's ends hold its neighbours' sites too: k_sweep_cached loads
 // them to stay (FP32 191-site rows 158 us, 171 streaming) and gives runs of
 // neighbours one XCD's L2 (BF16 92.3 -> 89.6 us, FP16 90.7 -> 86.9, FP32 the
-// same).  Small 3D boxes (kSmallSweep) in two arrays of FP64 or FP32 take
-// k_sweep whatever their rows: the runs of their few workgroups load the XCDs
-// unevenly (step with a sphere, FP64 50^3 17.8 us grouped, 15.5 streaming, 66^3
-// 27.9 / 26.0, FP32 66^3 19.3 / 17.6; but 16-bit 66^3 14.8 / 15.1, in one array
-// FP32 25.4 / 26.1, 2D FP64 300^2 11.0 / 12.1).
+// same).  Two arrays of FP64 or FP32 that outgrow the L2s (kGroupBytes) take
+// k_sweep whatever their rows in 2D and in 3D boxes of few workgroups
+// (kSmallSweep), whose runs load the XCDs unevenly.  Steps, grouped against
+// streaming: FP64 50^3 17.8 / 15.5 us, 66^3 27.9 / 26.0, FP32 66^3 19.3 / 17.6, 2D
+// with 20 disks FP64 590^2 25.7 / 23.3, FP32 801^2 24.7 / 22.3; but below it FP32
+// 41^3 12.2 / 12.5, FP64 300^2 16.6 / 17.4, and 16-bit 66^3 14.8 / 15.1, FP64 66^3
+// in one array 25.4 / 26.1.
 template <int Q, typename T, bool PART, int LAY, bool NTL, bool NEAR>
 __device__ __forceinline__ void sweep_run(int wg, const T* A, T* B, const SweepArgs<Q, typename Store<T>::C>& a,
                                           const SiteArgs<T>& sa) {
@@ -3148,6 +3150,8 @@ int sweep_cap(const lbm_ctx* c, int w, int occ) {
   return occ_ok(c, cap) ? cap : 0;
 }
 
+// Bytes of both arrays up to which the L2s (32 MB) hold most of them.
+constexpr size_t kGroupBytes = (size_t)18 << 20;
 // Sites below which a box is too few workgroups for the rules of larger ones.
 template <typename T>
 constexpr int kSmallSweep = sizeof(T) == 2 ? 500000 : 350000;
@@ -3162,6 +3166,9 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
   T* B = (T*)c->f[1 - c->cur];  // the same array under the AA pattern
   const SiteArgs<T> sa = site_args<Q, T>(c);
   const bool lines = (size_t)a.nx * sizeof(T) % 128 == 0;  // rows are whole cache lines
+  // loads of one box's sweep (see k_sweep)
+  const bool streaming = lines || (LAY == kLayAB && sizeof(T) > 2 && 2 * (size_t)Q * c->PS * sizeof(T) >= kGroupBytes &&
+                                   (Q == 9 || a.n < kSmallSweep<T>));
   if (w == 0) {
     if constexpr (sizeof(T) == 2 && LAY == kLayAB) {
       // two sites per lane, one wave per 128 sites of a row, while rows are
@@ -3198,7 +3205,6 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
                      (LAY != kLayAB || sizeof(T) == 4);
     const int block = a.n < 128 * kSweepBlock && occ == 0 ? 64 : row ? a.nx : kSweepBlock;
     const unsigned g = blocks_for(a.n, block);
-    const bool streaming = lines || (Q == 19 && LAY == kLayAB && sizeof(T) > 2 && a.n < kSmallSweep<T>);
     if constexpr (kNearSweep<T, LAY>) {
       if ((size_t)Q * c->PS * sizeof(T) > 0xffffffffu) {
         auto* kernel = lines ? (c->np > 0 ? k_sweep_wide<Q, T, true, LAY, true> : k_sweep_wide<Q, T, false, LAY, true>)
@@ -3219,8 +3225,7 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
   } else {
     const int64_t nt = c->ntiles;
     const unsigned g = (unsigned)(grid > 0 && grid < nt ? grid : nt);
-    // streaming loads for one box of whole-line rows, cached ones otherwise (as k_sweep)
-    const bool ntl = c->nbox == 1 && lines;
+    const bool ntl = c->nbox == 1 && streaming;
     if (c->np > 0 && ntl)
       k_sweep_tiles<Q, T, true, LAY, true><<<g, w, lds, c->stream>>>(A, B, a, sa, c->d_tiles, (int)nt,
                                                                       (const C*)c->d_fbt);

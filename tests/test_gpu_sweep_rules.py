@@ -54,3 +54,18 @@ def test_even_rows_with_two_sites_per_lane(storage, box):
     """Even rows that are not whole cache lines, inside and outside of one round of
     waves and on both sides of 350,000 sites (and an odd row)."""
     test_rows_of_their_own_workgroup(storage, False, box)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,box", [("fp64", (361, 363, 1)), ("fp64", (363, 361, 1)), ("fp64", (365, 364, 1)), ("fp32", (511, 511, 1)),
+                                         ("fp32", (517, 516, 1)), ("fp64", (39, 38, 39)), ("fp64", (41, 40, 38)), ("fp32", (49, 50, 50))])
+def test_both_sides_of_the_size_that_the_caches_hold(storage, box):
+    """Two arrays of FP64 or FP32 below and above 18 MiB, rows that are not whole
+    cache lines, against tiles of two widths with a persistent grid or without."""
+    q = 9 if box[2] == 1 else 19
+    w = [4 / 9] + [1 / 9] * 4 + [1 / 36] * 4 if q == 9 else [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12
+    f0 = wl.random_populations(w, (box[2], box[1], box[0]), 5, 0.01)
+    a = _run(q, box, storage, False, 0, (0, 0, 0), f0)
+    for shape in ((64, 0, 0), (512, 256, 4)):
+        for x, y in zip(a, _run(q, box, storage, False, 0, shape, f0)):
+            assert np.array_equal(x, y), (storage, box, shape)
