@@ -1800,8 +1800,9 @@ __global__ __launch_bounds__(256) void k_prepare(const int* __restrict__ own,
 // written only where they can change: at the sites of a particle whose shift
 // changed in this step (its new sites, and its old sites that no ball of it
 // covers any more, cleared or handed to the neighbour covering them) and, with
-// flags_all, at every ball site (after particles are added).  Every writer of
-// a flag computes it from the same final map, so they agree.
+// ADD, at every ball site (of the particles from `first` on, after some are
+// added).  Every writer of a flag computes it from the same final map, so they
+// agree.
 // ---------------------------------------------------------------------------
 // Kind of particle q's template at site (x, y, z) of its box, with q's
 // origin (og) and kind-grid half-width R: 0 unless the site is one of its
@@ -1945,16 +1946,16 @@ __device__ __forceinline__ void prepare_entries(uint8_t* __restrict__ flag, type
   }
 }
 
-template <int Q, typename T, bool NTS>
+template <int Q, typename T, bool NTS, bool ADD>
 __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict__ flag,
                                                              typename Store<T>::C* __restrict__ vel,
                                                              double* __restrict__ slot,
                                                              const typename Store<T>::C* __restrict__ drho,
                                                              T* __restrict__ S, DevParticles P, DevEntries E, Boxes BX,
                                                              double rho0, int pending, int lay, int split,
-                                                             int flags_all, int first) {
+                                                             int first) {
   __shared__ Neighbour s_nb[kNbrMax];
-  const int p = first + blockIdx.x / split, part = blockIdx.x % split;
+  const int p = (ADD ? first : 0) + blockIdx.x / split, part = blockIdx.x % split;
   const int tid = threadIdx.x;
   const Geo G = geo_of(BX, P, p);
   Prepared a;
@@ -1965,7 +1966,7 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
   a.b = rigid_body(P, p);
   a.jump = P.jump[p] != 0;
   a.moved = P.moved[p] != 0;
-  a.flags = flags_all != 0 || a.moved;
+  a.flags = ADD || a.moved;
   // interior entries come last and only write flags: skipped when the flags
   // stand as they are
   a.e0 = P.ent0[p];
@@ -3001,23 +3002,25 @@ Boxes boxes_arg(const lbm_ctx* c) {
 }
 
 // The IS substep of the step that just ran (pending = 1) and the records of
-// the ball sites of particles first .. np - 1 for the next sweep (with an owner
-// map, which knows every claim, of all particles).  Kind grids: up to eight
+// the ball sites for the next sweep: of every particle in a step (first = -1), of
+// particles first .. np - 1, a box that grew, after an add (with an owner map,
+// which knows every claim, of all particles).  Kind grids: up to eight
 // workgroups per particle (64 for large balls); owner map: one thread per entry.
 // With kind grids the sharing lists of those particles must be of their present
 // positions: a step's k_reduce or the upload of an added box writes them just
 // before, and nothing else keeps them.
 template <int Q, typename T, bool NTS>
-int launch_prepare_as(lbm_ctx* c, int pending, int flags_all, int first) {
+int launch_prepare_as(lbm_ctx* c, int pending, int first) {
   using C = typename Store<T>::C;
   if (c->grids) {
     // split workgroups per particle only while the particles alone leave the
     // GPU short of workgroups (about 8 per CU)
-    const int n = c->np - first;
+    const int n = c->np - std::max(first, 0);
     const int split = std::max(1, std::min(c->prep_split, 2048 / std::max(n, 1)));
-    k_prepare_grid<Q, T, NTS><<<n * split, kGridBlock, 0, c->stream>>>(
+    auto* kernel = first >= 0 ? k_prepare_grid<Q, T, NTS, true> : k_prepare_grid<Q, T, NTS, false>;
+    kernel<<<n * split, kGridBlock, 0, c->stream>>>(
         c->flag, (C*)c->vel, c->slot, (const C*)c->drho, (T*)c->f[c->cur], c->P, c->E, boxes_arg(c), c->prm.rho0,
-        pending, state_layout(c), split, flags_all, first);
+        pending, state_layout(c), split, first);
   } else {
     k_prepare<Q, T, NTS><<<blocks_for(c->nent), 256, 0, c->stream>>>(
         c->own, c->flag, (C*)c->vel, c->slot, (const C*)c->drho, (T*)c->f[c->cur], c->P, c->E, boxes_arg(c),
@@ -3037,10 +3040,10 @@ bool streaming_is(const lbm_ctx* c) {
 }
 
 template <int Q, typename T>
-int launch_prepare(lbm_ctx* c, int pending, int flags_all, int first) {
+int launch_prepare(lbm_ctx* c, int pending, int first) {
   if (c->nent == 0) return LBM_OK;
-  return streaming_is(c) ? launch_prepare_as<Q, T, true>(c, pending, flags_all, first)
-                         : launch_prepare_as<Q, T, false>(c, pending, flags_all, first);
+  return streaming_is(c) ? launch_prepare_as<Q, T, true>(c, pending, first)
+                         : launch_prepare_as<Q, T, false>(c, pending, first);
 }
 
 // The particles' part of a step of boxes with few particles (fuse_ok); c->cur
@@ -3307,7 +3310,7 @@ int launch_step(lbm_ctx* c) {
     HIP_TRY(hipGetLastError());
   }
   c->cur = 1 - c->cur;  // f[cur] now holds this step's post-collision state
-  if (c->np > 0) return launch_prepare<Q, T>(c, 1, 0, 0);
+  if (c->np > 0) return launch_prepare<Q, T>(c, 1, -1);
   return LBM_OK;
 }
 
@@ -3908,7 +3911,7 @@ static int add_impl(lbm_ctx* c, int32_t bx, int32_t n, const double* x, const do
   // flags and records of every ball site of the box, with nothing pending; the
   // other boxes' stand as their last step or add left them (their sharing lists
   // may be older: k_box and lbm_step_noalloc write none to the workspace)
-  const int prc = DISPATCH(c, launch_prepare, c, 0, 1, pbox0);
+  const int prc = DISPATCH(c, launch_prepare, c, 0, pbox0);
   if (prc != LBM_OK) return fail(prc);
   if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(LBM_EHIP);
   // fluid body force of every box: user value, plus the opposite of the
