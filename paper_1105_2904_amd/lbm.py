@@ -296,10 +296,12 @@ class Simulation:
 
     def forces(self):
         n = self.n_particles
-        out = np.empty((5, n, 3))
-        at, size = out.ctypes.data, 24 * n
-        _check(lib().lbm_forces(self.ctx, at, at + size, at + 2 * size, at + 3 * size, at + 4 * size), "lbm_forces")
-        return tuple(a.copy() for a in out)  # F, T, x, u, omega, each an array of its own
+        out = tuple([np.empty((n, 3)) for _ in range(5)])  # F, T, x, u, omega
+        # addresses by the buffer protocol, which refuses an empty array, before the
+        # call waits for the GPU
+        at = [ctypes.byref(ctypes.c_char.from_buffer(a)) for a in out] if n else [None] * 5
+        _check(lib().lbm_forces(self.ctx, *at), "lbm_forces")
+        return out
 
     def fields(self):
         rho = np.empty(self.N)
