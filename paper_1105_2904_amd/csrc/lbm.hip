@@ -1790,8 +1790,8 @@ __global__ __launch_bounds__(256) void k_prepare(const int* __restrict__ own,
 
 // ---------------------------------------------------------------------------
 // K5 with kind grids: the work of k_prepare, one to eight workgroups per
-// particle (up to 64 for balls of more than kSmallGrid bounding-box sites) (rows of
-// kGridBlock entries dealt round-robin; entries in raster order, so the
+// particle, up to 64 for balls of more than kSmallGrid bounding-box sites (runs of
+// 64 entries dealt round-robin; entries in raster order, so the
 // loads at their own sites are row-coalesced), with the owner of a site
 // settled without an owner map.  A site is owned by the lowest particle id among those whose
 // BS or IS entry lies on it at the new shifts (none on wall sites); only the
@@ -1994,9 +1994,11 @@ __global__ __launch_bounds__(kGridBlock) void k_prepare_grid(uint8_t* __restrict
 // workgroup per box, in one launch instead of three (four).  What such a box
 // needs of each is a chain of a few dependent loads, and a launch boundary
 // costs 1.9 us; within a workgroup the stages hand their results over in LDS.
-// Teams of 256 threads take the particles in turn for the sums (as k_reduce
-// does, in the same order); all of them share the prepare pass; one more wave
-// finds the close pairs and runs the closure network meanwhile.  The largest
+// Teams of 256 threads take the particles in turn for the sums (in the order of
+// k_reduce<256>; k_reduce<128>, for more than 1,024 small particles, adds the
+// entries past the first 128 of a particle in another); one more wave finds the
+// close pairs and runs the closure network meanwhile; then all waves share the
+// prepare pass.  The largest
 // balls' scattered IS stores want more than one CU: those keep the separate
 // kernels (fuse_ok).  One disk in 64^2 FP64: step 14.6 -> 9.9 us; 16 boxes of
 // two disks with the closure 36.4 -> 14.8 us; one sphere in 100 x 100 x 160
@@ -2377,8 +2379,8 @@ __global__ __launch_bounds__(kTeam * few_teams(CLO) + 64) void k_box(
     P.jump[p] = pr.jump;
     P.moved[p] = pr.moved;
   }
-  // the prepare pass: every whole team's waves on each particle in turn, or
-  // shared out when there are more particles than one
+  // the prepare pass: the waves, the last one too, in n equal groups, a particle
+  // each (up to n - 1 waves are left over)
   const int waves = (int)blockDim.x / 64, per = waves / n;
   for (int q = 0; q < n; q++) {
     if (wv < q * per || wv >= (q + 1) * per) continue;
@@ -2892,7 +2894,8 @@ struct lbm_ctx {
   int sweep_occ;            // cap on resident sweep workgroups per CU (0: none)
   int lds_cu, lds_block;    // LDS bytes per CU and the most one workgroup may reserve
   int device;               // the device the context was created on
-  bool row_ok;              // one box whose ny and nz fit a launch grid: width 0 covers it
+  bool row_ok;              // one box whose ny and nz fit a launch grid's: width 0 is taken (longer boxes have
+                            // always been refused it, though its own grids have one dimension now)
   std::vector<int> h_box;   // box of every particle
   std::vector<double> fbb;  // [nbox][3] fluid body force density
   // step graph

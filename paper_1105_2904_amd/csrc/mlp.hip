@@ -33,11 +33,11 @@ constexpr int kWaves = 4;
 // Bound by its vector instructions: per 16-row tile 32 tanh a lane, each an
 // exponential, a reciprocal and four ordinary operations, against 24 MFMAs and
 // 640 bytes.  So everything else is kept off the vector unit: the weight
-// operands and biases stay in registers, the tile index and with it every
-// address and bound in scalar ones, and 168 registers a lane let the products
-// land where the tanh reads them (at 128 the compiler put them in
-// accumulators, one more move each).  4,194,304 rows: 179 -> 160 us (253
-// TFLOP/s of the products).
+// operands and biases stay in registers, and the tile index and with it every
+// address and bound in scalar ones.  The launch bound leaves the compiler 168
+// registers a lane, of which it takes 119 (four waves a SIMD all the same);
+// bound to 128 it put the products in accumulators, one more move each before
+// the tanh.  4,194,304 rows: 179 -> 160 us (253 TFLOP/s of the products).
 __global__ __launch_bounds__(256, 3) void k_mlp_forward(const float* __restrict__ P, const float* __restrict__ X,
                                                         float* __restrict__ Y, int64_t n) {
   __shared__ mlp::Weights w;
@@ -223,9 +223,11 @@ __device__ __forceinline__ _Float16 float_product(float a, float b) {
 // v, of which the compiler knows nothing: what a loop derives from it (LDS
 // addresses, above all) is computed there again and not kept in registers, of
 // which sixteen waves leave each lane 128 (without it 33 loads and 9
-// stores of spilled values in a training step, now 13 in all: a step of 256
-// rows 10.3 -> 9.9 us, of 64 7.1 -> 5.6; the gradient spilled 24 and spills none
-// now: 44,672 rows 21.3 -> 17.4 us, 512 14.1 -> 11.2).
+// stores of spilled values in a training step, now 13 of each in the whole
+// kernel: a step of 256 rows 10.3 -> 9.9 us, of 64 7.1 -> 5.6; the gradient
+// spilled 24 and spills none now: 44,672 rows 21.3 -> 17.4 us, 512 14.1 -> 11.2).
+// Batches of more than 256 rows, whose sums live across the tile phase, still
+// spill 77 registers (512 rows 20.2 -> 19.8 us).
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -693,7 +695,9 @@ int lbm_mlp_forward(const float* d_params, const float* d_x, float* d_y, int64_t
   // every workgroup first stages the weights (about 5 us), so up to 2^17 tiles
   // there are only as many as fit the chip at once (4 per CU: 200,000 rows 14
   // us, against 18 with 2,048 and 26 with 4,096); beyond, twice as many share
-  // out the CUs' unequal speed (4,194,304 rows: 160 us, against 168 and 163)
+  // out the CUs' unequal speed (4,194,304 rows: 160 us, against 168 and 163; at
+  // the line itself 2,097,152 rows 85.8 us with 1,024, 16 rows more 82.7 with
+  // 2,048)
   const int64_t most = tiles <= (int64_t)1 << 17 ? 1024 : 2048;
   const int64_t blocks = std::min<int64_t>((tiles + kWaves - 1) / kWaves, most);
   k_mlp_forward<<<(unsigned)blocks, 256, 0, (hipStream_t)hip_stream>>>(d_params, d_x, d_y, n);
