@@ -845,6 +845,10 @@ __host__ __device__ constexpr int x_shifted_before(int i) {
   return n;
 }
 
+// LDS of k_sweep_pairs: a wave's first and last word of each of those populations.
+template <int Q>
+constexpr size_t kPairShared = sizeof(uint32_t) * (kSweepBlock / 64) * 2 * x_shifted_before<Lattice<Q>>(Q);
+
 template <int Q, typename T, bool PART>
 __global__ __launch_bounds__(kSweepBlock) void k_sweep_pairs(const T* __restrict__ A, T* __restrict__ B,
                                                               SweepArgs<Q, float> a, SiteArgs<T> sa) {
@@ -853,6 +857,7 @@ __global__ __launch_bounds__(kSweepBlock) void k_sweep_pairs(const T* __restrict
   constexpr int kWaves = kSweepBlock / 64;
   constexpr int kShift = x_shifted_before<L>(Q);
   __shared__ uint32_t s_edge[kWaves][2][kShift];  // [wave][first, last word][shifted population]
+  static_assert(sizeof(s_edge) == kPairShared<Q>, "what launch_sweep_as leaves to it");
   const int lane = (int)threadIdx.x & 63;
   // wave-uniform: the row chunk of this wave (the last one for waves past it)
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -3190,10 +3195,13 @@ int launch_sweep_as(lbm_ctx* c, int w, int grid, int occ) {
       const bool round = Q == 19 && a.nx % 2 == 0 && a.n >= 350000 && waves <= kPairWaves && (c->np > 0 || a.nx % 8 == 0);
       if ((lines && a.nx > 64) || round) {
         const unsigned g = (unsigned)((waves + kSweepBlock / 64 - 1) / (kSweepBlock / 64));
+        // what the cap reserves and the kernel's own LDS fit one workgroup (at a cap
+        // of 1 the former is all there is, and the launch aborted the queue)
+        const size_t own = std::min(lds, (size_t)c->lds_block - kPairShared<Q>);
         if (c->np > 0)
-          k_sweep_pairs<Q, T, true><<<g, kSweepBlock, lds, c->stream>>>(A, B, a, sa);
+          k_sweep_pairs<Q, T, true><<<g, kSweepBlock, own, c->stream>>>(A, B, a, sa);
         else
-          k_sweep_pairs<Q, T, false><<<g, kSweepBlock, lds, c->stream>>>(A, B, a, sa);
+          k_sweep_pairs<Q, T, false><<<g, kSweepBlock, own, c->stream>>>(A, B, a, sa);
         HIP_TRY(hipGetLastError());
         return LBM_OK;
       }

@@ -69,3 +69,17 @@ def test_both_sides_of_the_size_that_the_caches_hold(storage, box):
     for shape in ((64, 0, 0), (512, 256, 4)):
         for x, y in zip(a, _run(q, box, storage, False, 0, shape, f0)):
             assert np.array_equal(x, y), (storage, box, shape)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,q,box", [("fp16", 19, (128, 17, 16)), ("bf16", 19, (256, 9, 7)), ("fp16", 9, (192, 61, 1)),
+                                           ("fp32", 19, (64, 24, 24)), ("fp64", 9, (61, 60, 1))])
+def test_cap_of_one_workgroup(storage, q, box):
+    """A cap of 1 reserves all of a compute unit's LDS for one workgroup, the sweep
+    with two sites per lane, which has LDS of its own, among them."""
+    w = [4 / 9] + [1 / 9] * 4 + [1 / 36] * 4 if q == 9 else [1 / 3] + [1 / 18] * 6 + [1 / 36] * 12
+    f0 = wl.random_populations(w, (box[2], box[1], box[0]), 5, 0.01)
+    a = _run(q, box, storage, False, 0, (0, 0, 1), f0)
+    for shape in ((0, 0, 0), (64, 0, 1)):
+        for x, y in zip(a, _run(q, box, storage, False, 0, shape, f0)):
+            assert np.array_equal(x, y), (storage, box, shape)
